@@ -24,6 +24,19 @@ Regions of z = v + i a (float32 unless noted):
   are below 5e-8 of H and are dropped.
 * core with larger damping: Weideman's 32-term rational expansion of w(z)
   (J.A.C. Weideman, SIAM J. Numer. Anal. 31 (1994) 1497) in float64.
+* near zone of the split sums, a <= 0.15 and |v| < NEAR_V: with G(v) = 2 v F(v) - 1
+  every damping term follows from g = (2/sqrt(pi)) G by recurrence (F' = -G,
+  F^(n+1) = -2 v F^(n) - 2 n F^(n-1)):
+      H = exp(a^2-u) cos(2av) + a [g + a^2 (s/3 + g (1 - 2u/3))
+          + a^4 (s (7/30 - u/15) + g (1/2 - 2u/3 + 2u^2/15))],  s = 2/sqrt(pi),
+  so one table serves H and its derivatives.  g is piecewise cubic in |v|
+  (intervals of 1/NEAR_INV, Chebyshev nodes, 4 floats each).
+* far zone of the split sums, v >= FAR_V and a <= FAR_AV v: with w = 1/v^2, b = a^2
+      H = (a/sqrt(pi)) w sum_{n<=5} w^n P_n(b),
+  P_n of degree n: the asymptotic coefficients of w(z) for n <= 3, the last two
+  fitted (minimax on w <= 1/FAR_V^2, b w <= FAR_AV^2).  The same form with its
+  own polynomials serves a dH/da, and X = H + a dH/da + v dH/dv with one
+  more factor w (n <= 4 there).
 
 Run:  python gen_voigt_consts.py > voigt_consts.h
 """
@@ -157,6 +170,104 @@ def pw_check_L(h, tab):
     return worst
 
 
+NEAR_INV = 16
+NEAR_V = 8.0
+FAR_V = 5.5
+FAR_AV = 0.2
+FAR_N = 6          # powers w^1 .. w^6
+
+
+def near_table():
+    """Cubics of (2/sqrt(pi)) G in the fraction of each interval of |v|."""
+    n = int(NEAR_V * NEAR_INV) + 1
+    x = 0.5 * (1.0 - np.cos((np.arange(4) + 0.5) * np.pi / 4))
+    tab = np.zeros((n, 4))
+    for k in range(n):
+        v = np.maximum((k + x) / NEAR_INV, 1e-30)
+        tab[k] = np.linalg.solve(np.vander(x, 4, increasing=True), -2.0 / np.sqrt(np.pi) * dawson_derivs(v)[1])
+    return tab
+
+
+def near_check(tab):
+    """Max relative error of the float32 near-zone H against wofz."""
+    from scipy.special import wofz
+    f = np.float32
+    s = 2.0 / np.sqrt(np.pi)
+    t32 = tab.astype(f)
+    worst = {}
+    for a in (A_SMALL, 0.1, A_TINY, 1e-2, 1e-3, 1e-5):
+        v = np.linspace(0.0, NEAR_V, 40001)[:-1].astype(f)
+        x = v * f(NEAR_INV)
+        k = x.astype(np.int32)
+        r = x - k.astype(f)
+        q = t32[k]
+        g = ((q[:, 3] * r + q[:, 2]) * r + q[:, 1]) * r + q[:, 0]
+        u, a2 = v * v, f(a * a)
+        h3 = f(s / 3) + g * (1 - f(2 / 3) * u)
+        h5 = f(7 * s / 30) - f(s / 15) * u + g * (f(0.5) - f(2 / 3) * u + f(2 / 15) * u * u) if a > A_TINY else f(0)
+        y = a2 * u
+        cs = (((f(2 / 315) * y - f(4 / 45)) * y + f(2 / 3)) * y - 2) * y + 1
+        H = np.exp2((a2 - u) * f(1.4426950408889634)).astype(np.float64) * cs + a * (g + a2 * (h3 + a2 * h5))
+        ref = wofz(v.astype(np.float64) + 1j * np.sqrt(np.float64(a2))).real
+        worst[a] = np.max(np.abs(H - ref) / ref)
+    return worst
+
+
+def far_fit(kind):
+    """Polynomials of the far zone: coefficients {(m, k): c} of w^m (b w)^k and the max relative
+    error.  kind 0: H, 1: a dH/da, 2: X / w."""
+    from math import comb
+    from scipy.special import wofz
+    n, N = 60, FAR_N - 1
+    ch = 0.5 * (1.0 - np.cos((np.arange(n) + 0.5) * np.pi / n))
+    W, Q = (z.ravel() for z in np.meshgrid(ch / FAR_V ** 2, ch * FAR_AV ** 2, indexing="ij"))
+    v = 1.0 / np.sqrt(W)
+    a = np.sqrt(Q) * v
+    z = wofz(v + 1j * a)
+    H, L = z.real, z.imag
+    aHa = 2.0 * a * (v * L + a * H) - 2.0 * a / np.sqrt(np.pi)
+    X = H + aHa - 2.0 * v * (v * H - a * L)
+    top = N if kind < 2 else N - 1
+    y = (H, aHa, X / W)[kind] * np.sqrt(np.pi) / (a * W)
+    exact = {}
+    for m in range(N + 1):          # (2m-1)!!/2^m Re[i z^-(2m+1)], expanded in a/v
+        dd = np.prod(np.arange(1.0, 2 * m, 2.0)) / 2.0 ** m
+        for k in range(N + 1 - m):
+            c = dd * comb(2 * m + 2 * k + 1, 2 * k + 1) * (-1.0) ** k
+            if kind == 0:
+                exact[m, k] = c
+            elif kind == 1:
+                exact[m, k] = c * (1 + 2 * k)
+            elif m >= 1:
+                exact[m - 1, k] = -2.0 * m * c
+    keys = [(t - k, k) for t in range(top + 1) for k in range(t + 1)]
+    out = {e: exact[e] for e in keys if sum(e) <= top - 2}
+    free = [e for e in keys if e not in out]
+    res = y - sum(c * W ** m * Q ** k for (m, k), c in out.items())
+    A = np.stack([W ** m * Q ** k for m, k in free], 1) / y[:, None]
+    sc = np.abs(A).max(0)
+    wt = np.ones(y.size)
+    for _ in range(60):
+        c = np.linalg.lstsq(A / sc * wt[:, None], res / y * wt, rcond=None)[0]
+        e = np.abs(A / sc @ c - res / y)
+        wt = wt * (0.3 + e / e.max()) ** 0.3
+        wt /= wt.mean()
+    out.update(zip(free, c / sc))
+    return out, e.max()
+
+
+def far_arrays():
+    out = []
+    for kind, tag in ((0, "H"), (1, "A"), (2, "X")):
+        c, err = far_fit(kind)
+        top = max(m for m, _ in c)
+        flat = [c[n - k, k] for n in range(top + 1) for k in range(n + 1)]
+        out.append("/* far zone, %s: P_n, n = 0..%d, ascending powers of b; max relative error %.1e */"
+                   % (("H", "a dH/da", "X")[kind], top, err))
+        out.append(arr("PZ_FAR_%s" % tag, flat))
+    return out
+
+
 def arr(name, c, typ="float", fmt="%.9ef"):
     return "__device__ static constexpr %s %s[%d] = {%s};" % (typ, name, len(c), ", ".join(fmt % x for x in c))
 
@@ -192,6 +303,20 @@ def main():
     out.append("__device__ static constexpr float PZ_PW_MU_TAB[%d] = {" % (PW_N * 16))
     out += ["    " + ", ".join("%.9ef" % x for x in row) + "," for row in tab_mu]
     out.append("};")
+    near = near_table()
+    out.append("/* near zone: cubics of (2/sqrt(pi)) (2 v F(v) - 1), %d intervals of 1/%d; max relative error of H against"
+               % (len(near), NEAR_INV))
+    out.append("   wofz: %s */" % ", ".join("a=%g: %.1e" % (k, v) for k, v in near_check(near).items()))
+    out.append("static constexpr int PZ_NEAR_N = %d;" % len(near))
+    out.append("#define PZ_NEAR_INV %.1ff" % NEAR_INV)
+    out.append("#define PZ_NEAR_V %.1ff" % NEAR_V)
+    out.append("__device__ static constexpr float PZ_NEAR_TAB[%d] = {" % (4 * len(near)))
+    out += ["    " + ", ".join("%.9ef" % x for x in row) + "," for row in near]
+    out.append("};")
+    out.append("#define PZ_FAR_V %.1f" % FAR_V)
+    out.append("#define PZ_FAR_AV %.1f" % FAR_AV)
+    out.append("static constexpr int PZ_FAR_N = %d;" % FAR_N)
+    out += far_arrays()
     L, c = weideman(N_W)
     out.append("static constexpr int PZ_WEID_N = %d;" % N_W)
     out.append("#define PZ_WEID_L %.17e" % L)

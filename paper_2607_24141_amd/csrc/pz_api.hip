@@ -88,6 +88,24 @@ Window line_window(double lam_l, double lf, double r1, double h, int N, double W
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Whether a plan's line sums are split by detuning (pz_split.h).
+// The split sums are the faster ones everywhere (1500-1700 nm, 5.3 lines per
+// pixel, 113-pixel windows: 0.90 against 1.26 ms; 300-1000 nm, 180-600 pixels:
+// 32 against 54 ms; eight stars of 1-24 lines per pixel: 4.9 against 9.0 ms).
+// What sends a plan to the direct kernel is the conditioning of its gradients,
+// not its time: with more than ~5.5 lines per pixel and windows this narrow, a
+// star of ordinary abundances is optically thick at its first depth at every
+// wavelength, its line gradients are what is left of surface terms that cancel
+// to 1e-4 and less, and one float32 rounding of kappa moves them by 1e-5 to
+// 1e-4 of their norm (measured on such stars; 1e-7 to 4e-6 at lower
+// densities).  Neither order of summation is the more exact there, so those
+// plans keep the one their results were always taken with, bit for bit.
+bool split_rule(int N, int L, int D, int64_t evals) {
+    if (L == 0) return true;
+    const double window_px = (double)evals / D / L, per_px = (double)L / N;
+    return window_px >= 165.0 || per_px <= 5.5;
+}
+
 }  // namespace
 
 extern "C" {
@@ -187,18 +205,23 @@ int pz_plan_create(const pz_grid* grid, const pz_lines* lines, int32_t n_species
     std::vector<int> pmax_hi(L), smin_lo(L);
     for (int k = 0; k < L; ++k) pmax_hi[k] = k ? std::max(pmax_hi[k - 1], ihi[k]) : ihi[k];
     for (int k = L - 1; k >= 0; --k) smin_lo[k] = (k < L - 1) ? std::min(smin_lo[k + 1], ilo[k]) : ilo[k];
+    auto tile_lines = [&](int t, int px, int* first, int* last) {
+        const int start = t * px, end = std::min(N - 1, start + px - 1);
+        *first = (int)(std::lower_bound(pmax_hi.begin(), pmax_hi.end(), start) - pmax_hi.begin());
+        *last = std::max(*first, (int)(std::upper_bound(smin_lo.begin(), smin_lo.end(), end) - smin_lo.begin()));
+    };
     std::vector<int> tfirst(n_tiles), tlast(n_tiles);
     for (int t = 0; t < n_tiles; ++t) {
-        const int start = t * tile_px, end = std::min(N - 1, start + tile_px - 1);
-        const int f = (int)(std::lower_bound(pmax_hi.begin(), pmax_hi.end(), start) - pmax_hi.begin());
-        const int g = (int)(std::upper_bound(smin_lo.begin(), smin_lo.end(), end) - smin_lo.begin());
-        tfirst[t] = f;
-        tlast[t] = std::max(f, g);
-        // the opacity kernel addresses a tile's parameter rows with 32-bit byte offsets
+        tile_lines(t, tile_px, &tfirst[t], &tlast[t]);
+        // the opacity kernels address a tile's parameter rows with 32-bit offsets
         if ((long long)(tlast[t] - tfirst[t]) * D >= (1LL << 28))
             return fail(PZ_E_SHAPE, "%d lines overlap pixel tile %d: lines x n_depth per tile must be below 2^28",
                         tlast[t] - tfirst[t], t);
     }
+    const bool split = split_rule(N, L, D, evals);
+    const int n_t32 = (N + TILE - 1) / TILE;
+    std::vector<int> t32f(n_t32), t32l(n_t32);
+    for (int t = 0; t < n_t32; ++t) tile_lines(t, TILE, &t32f[t], &t32l[t]);
     // species lists over sorted lines (ascending sorted index)
     std::vector<int> sp_off(S + 1, 0), sp_idx(L);
     for (int k = 0; k < L; ++k) sp_off[(spion[k] >> 1) + 1]++;
@@ -230,22 +253,28 @@ int pz_plan_create(const pz_grid* grid, const pz_lines* lines, int32_t n_species
     const size_t o_part = take((size_t)(S + 1) * n_rchunk * 4);
     const size_t o_seed = take((size_t)Npad * 4);
     const size_t o_order = take((size_t)n_tiles * 4), o_qctr = take(4), o_wany = take(4);
+    const size_t o_t32f = take((size_t)n_t32 * 4), o_t32l = take((size_t)n_t32 * 4), o_t32o = take((size_t)n_t32 * 4);
     const bool scatter_ws = (opts->flags & PZ_FLAG_SCATTERING) != 0;
     const size_t o_sc = scatter_ws ? take((size_t)SC_WS_ARRAYS * D * Npad * 8) : 0;
     const size_t o_sci = scatter_ws ? take((size_t)3 * Npad * 4) : 0;
     // Voigt evaluations per tile (orders the batched opacity work)
-    std::vector<int64_t> tcost(n_tiles, 0);
-    for (int k = 0; k < L; ++k) {
-        if (ihi[k] < ilo[k]) continue;
-        for (int t = ilo[k] / tile_px; t <= ihi[k] / tile_px; ++t) {
-            const int a0 = std::max(ilo[k], t * tile_px), a1 = std::min(ihi[k], t * tile_px + tile_px - 1);
-            tcost[t] += (int64_t)(a1 - a0 + 1) * D;
+    auto tile_costs = [&](int px, int n) {
+        std::vector<int64_t> cost(n, 0);
+        for (int k = 0; k < L; ++k) {
+            if (ihi[k] < ilo[k]) continue;
+            for (int t = ilo[k] / px; t <= ihi[k] / px; ++t) {
+                const int a0 = std::max(ilo[k], t * px), a1 = std::min(ihi[k], t * px + px - 1);
+                cost[t] += (int64_t)(a1 - a0 + 1) * D;
+            }
         }
-    }
+        return cost;
+    };
+    // the tiles the plan's opacity kernels use
+    const std::vector<int64_t> tcost = split ? tile_costs(TILE, n_t32) : tile_costs(tile_px, n_tiles);
     pz_plan* p = new (std::nothrow) pz_plan();
     if (!p) return fail(PZ_E_NOMEM, "host allocation failed");
     std::memset(p, 0, sizeof *p);
-    p->tile_cost = new (std::nothrow) int64_t[n_tiles];
+    p->tile_cost = new (std::nothrow) int64_t[tcost.size()];
     if (!p->tile_cost) {
         delete p;
         return fail(PZ_E_NOMEM, "host allocation failed");
@@ -315,7 +344,12 @@ int pz_plan_create(const pz_grid* grid, const pz_lines* lines, int32_t n_species
     p->seed = (float*)(base + o_seed);
     p->tile_order = (int*)(base + o_order);
     p->qctr = (int*)(base + o_qctr);
-    std::vector<int> torder(n_tiles);
+    p->split = split;
+    p->n_t32 = n_t32;
+    p->t32_first = (int*)(base + o_t32f);
+    p->t32_last = (int*)(base + o_t32l);
+    p->t32_order = (int*)(base + o_t32o);
+    std::vector<int> torder(tcost.size());
     std::iota(torder.begin(), torder.end(), 0);
     std::stable_sort(torder.begin(), torder.end(), [&](int a, int b) { return tcost[a] > tcost[b]; });
     p->grid_opacity = opacity_grid(tile_px, opts->center_eta > 0.0);
@@ -338,7 +372,9 @@ int pz_plan_create(const pz_grid* grid, const pz_lines* lines, int32_t n_species
     if (ue == hipSuccess) ue = up(p->tile_first, tfirst.data(), (size_t)n_tiles * 4);
     if (ue == hipSuccess) ue = up(p->tile_last, tlast.data(), (size_t)n_tiles * 4);
     if (ue == hipSuccess) ue = up(p->sp_off, sp_off.data(), (size_t)(S + 1) * 4);
-    if (ue == hipSuccess) ue = up(p->tile_order, torder.data(), (size_t)n_tiles * 4);
+    if (ue == hipSuccess) ue = up(split ? p->t32_order : p->tile_order, torder.data(), torder.size() * 4);
+    if (ue == hipSuccess) ue = up(p->t32_first, t32f.data(), (size_t)n_t32 * 4);
+    if (ue == hipSuccess) ue = up(p->t32_last, t32l.data(), (size_t)n_t32 * 4);
     // workspaces start defined (pixels beyond N in the padded rows stay zero)
     if (ue == hipSuccess) ue = hipMemset(p->kappa, 0, (size_t)D * Npad * 4);
     if (ue == hipSuccess) ue = hipMemset(p->gk, 0, (size_t)D * Npad * 4);
@@ -511,6 +547,13 @@ StarDev make_star(const pz_plan* p, const pz_atmos* atm, const pz_params* par) {
     s.xlim = p->xlim;
     s.wide_a = p->wide_a;
     s.wide_any = p->wide_any;
+    s.split = p->split;
+    s.xfar = reinterpret_cast<float*>(p->wide_a);
+    s.window_cm = p->window_nm * 1.0e-7;
+    s.n_t32 = p->n_t32;
+    s.t32_first = p->t32_first;
+    s.t32_last = p->t32_last;
+    s.t32_order = p->t32_order;
     s.inv_kcl = p->inv_kcl;
     s.center_eta = p->center_eta;
     s.center = p->center_eta > 0.0;

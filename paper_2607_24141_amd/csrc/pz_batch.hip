@@ -32,6 +32,7 @@ enum Phase {
     PH_OP32,       // (star, tile) of stars with 32-pixel tiles, decreasing cost, atomic queue
     PH_OP64,       // ... 64-pixel tiles
     PH_OP128,      // ... 128-pixel tiles
+    PH_SPLIT,      // (star, 32-pixel tile) of stars with split sums, decreasing cost
     PH_FLUX,       // (star, 512 pixels)
     PH_SEED,       // (star, 512 pixels): chi^2 seed for stars with a target
     PH_LOSS,       // (star): chi^2 value, one 1024-thread workgroup
@@ -75,10 +76,10 @@ __global__ __launch_bounds__(512) void kb_pop(const StarDev* __restrict__ stars,
 }
 
 __global__ __launch_bounds__(512) void kb_lines(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n) {
-    __shared__ double red[3 * 512];
+    __shared__ double red[4 * 512];
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = uniform_item(items, it);
-        const double3 bnd = damp_bounds(stars[w.x], red);
+        const DampBounds bnd = damp_bounds(stars[w.x], red);
         dev_line_consts(stars[w.x], w.y * 512 + threadIdx.x, bnd);
     }
 }
@@ -95,17 +96,20 @@ __global__ __launch_bounds__(512) void kb_params(const StarDev* __restrict__ sta
 // ANYCT: some star of the batch uses the centre test (the LDS holds its rows);
 // G: depth-group slots (at least D / (64 / WPX) for every star); FG: exactly
 // D / (64 / WPX) for every star.
-template <int WPX, bool ANYCT, int G, bool FG>
-__global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void kb_opacity(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n, int* ctr) {
+// NTH: threads per workgroup, 512 for a whole tile or a part of it (items are
+// taken in parts then).
+template <int WPX, bool ANYCT, int G, bool FG, int NTH>
+__global__ __launch_bounds__(NTH) PZ_OPACITY_WAVES(WPX) void kb_opacity(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n, int* ctr) {
     PZ_OPACITY_LDS(WPX, ANYCT, sm);
     __shared__ int s_it;
     load_pw_table(sm.pw, false);                       // visible after the first item fetch's barrier
     for (;;) {
+        constexpr int PARTS = 512 / NTH;
         const int it = next_item(ctr, &s_it);
-        if (it >= n) return;
-        const int2 w = uniform_item(items, it);
+        if (it >= n * PARTS) return;
+        const int2 w = uniform_item(items, it / PARTS);
         const StarDev& s = stars[w.x];
-        dev_opacity_tile<WPX, false, ANYCT, G, false, FG>(s, w.y, s.chunk, sm);
+        dev_opacity_tile<WPX, false, ANYCT, G, false, FG, NTH>(s, w.y, it % PARTS, s.chunk, sm);
     }
 }
 
@@ -118,8 +122,31 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void kb_opacity_wide(con
     for (int it = blockIdx.x; it < n; it += gridDim.x) {
         const int2 w = uniform_item(items, it);
         const StarDev& s = stars[w.x];
-        dev_opacity_tile<WPX, true, ANYCT, opacity_max_groups<WPX>(), false>(s, w.y, s.chunk, sm);
+        dev_opacity_tile<WPX, true, ANYCT, opacity_max_groups<WPX>(), false>(s, w.y, 0, s.chunk, sm);
     }
+}
+
+// Split sums: one workgroup per (star, tile) item, dispatched in order of decreasing cost.
+__global__ __launch_bounds__(FAR_WAVES * WAVE) void kb_opacity_far(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ FarLds lds;
+    const int2 w = uniform_item(items, blockIdx.x);
+    dev_opacity_far(stars[w.x], w.y, lds);
+}
+
+// blockIdx.y: the depth groups of the tile (enough for the deepest star).
+__global__ __launch_bounds__(256) void kb_opacity_near(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ float4 near_tab[PZ_NEAR_N];
+    __shared__ float4 pw[PZ_PW_LDS];
+    const int2 w = uniform_item(items, blockIdx.x);
+    const StarDev& s = stars[w.x];
+    if ((int)blockIdx.y >= near_parts(s.D)) return;
+    load_near_table(near_tab);
+    load_pw_table(pw, false);
+    __syncthreads();
+    if (s.center)
+        dev_opacity_near<NEAR_G, true>(s, w.y, blockIdx.y, near_tab, pw);
+    else
+        dev_opacity_near<NEAR_G, false>(s, w.y, blockIdx.y, near_tab, pw);
 }
 
 __global__ __launch_bounds__(512) void kb_flux(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n) {
@@ -228,9 +255,9 @@ size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 template <bool ANYCT>
 static hipError_t batch_opacity_occupancy(int* occ) {
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[0], kb_opacity<4, ANYCT, 4, true>, 512, 0);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[1], kb_opacity<8, ANYCT, 9, true>, 512, 0);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[2], kb_opacity<16, ANYCT, 19, false>, 512, 0);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[0], kb_opacity<4, ANYCT, 4, true, 512>, 512, 0);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[1], kb_opacity<8, ANYCT, 9, true, 512>, 512, 0);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[2], kb_opacity<16, ANYCT, 19, false, 512>, 512, 0);
     return e;
 }
 
@@ -257,18 +284,33 @@ struct pz_batch {
 // One phase's opacity launches: the main pass with the fewest depth-group
 // slots that hold every star's D / (64 / WPX) groups (with no empty slot when
 // every star has the same group count), then the wide pass.
-template <int WPX, bool ANYCT>
-static void batch_opacity_wpx(const pz_batch* bt, int n, const int2* items, int* ctr, int grid, hipStream_t st) {
+template <int WPX, bool ANYCT, int NTH>
+static void batch_opacity_main(const pz_batch* bt, int n, const int2* items, int* ctr, int grid, hipStream_t st) {
     constexpr int GB = opacity_max_groups<WPX>();
     const int ng = bt->max_d / (64 / WPX);             // <= GB: D <= MAXD
     const bool same = bt->min_d / (64 / WPX) == ng;
     if (ng == GB)
-        same ? kb_opacity<WPX, ANYCT, GB, true><<<grid, 512, 0, st>>>(bt->stars, items, n, ctr)
-             : kb_opacity<WPX, ANYCT, GB, false><<<grid, 512, 0, st>>>(bt->stars, items, n, ctr);
+        same ? kb_opacity<WPX, ANYCT, GB, true, NTH><<<grid, NTH, 0, st>>>(bt->stars, items, n, ctr)
+             : kb_opacity<WPX, ANYCT, GB, false, NTH><<<grid, NTH, 0, st>>>(bt->stars, items, n, ctr);
     else if (ng == GB - 1 && same)
-        kb_opacity<WPX, ANYCT, GB - 1, true><<<grid, 512, 0, st>>>(bt->stars, items, n, ctr);
+        kb_opacity<WPX, ANYCT, GB - 1, true, NTH><<<grid, NTH, 0, st>>>(bt->stars, items, n, ctr);
     else
-        kb_opacity<WPX, ANYCT, GB - 1, false><<<grid, 512, 0, st>>>(bt->stars, items, n, ctr);
+        kb_opacity<WPX, ANYCT, GB - 1, false, NTH><<<grid, NTH, 0, st>>>(bt->stars, items, n, ctr);
+}
+
+// A batch with fewer than two tiles per workgroup slot is over when its
+// heaviest tiles are (8.3 ms for 885 tiles of five stars, 3.9 of issue): those
+// go out as two workgroups of four wavefronts each, which spreads a heavy
+// tile's wavefronts over twice the SIMDs (an eight-star batch forward +
+// backward: 17.8 ms against 20.1; parts of two wavefronts, whose staging of
+// every line serves only 16 pixels, 22.4).  The wavefronts do what they do in
+// a whole tile, so the results are the same bits.
+template <int WPX, bool ANYCT>
+static void batch_opacity_wpx(const pz_batch* bt, int n, const int2* items, int* ctr, int grid, hipStream_t st) {
+    if (n < 2 * grid)
+        batch_opacity_main<WPX, ANYCT, 256>(bt, n, items, ctr, 2 * grid, st);
+    else
+        batch_opacity_main<WPX, ANYCT, 512>(bt, n, items, ctr, grid, st);
     kb_opacity_wide<WPX, ANYCT><<<grid, 512, 0, st>>>(bt->stars, items, n);
 }
 
@@ -329,8 +371,8 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
         for (int k = 0; k < (s.S * s.D + 511) / 512; ++k) items[PH_POP].push_back({b, k});
         for (int k = 0; k < (s.L + 511) / 512; ++k) items[PH_LINES].push_back({b, k});
         for (long k = 0; k < (nld + PARAM_ITEM - 1) / PARAM_ITEM; ++k) items[PH_PARAMS].push_back({b, (int)k});
-        const int ph_op = s.tile_px == 32 ? PH_OP32 : (s.tile_px == 64 ? PH_OP64 : PH_OP128);
-        for (int t = 0; t < s.n_tiles; ++t) items[ph_op].push_back({b, t});
+        const int ph_op = s.split ? PH_SPLIT : s.tile_px == 32 ? PH_OP32 : (s.tile_px == 64 ? PH_OP64 : PH_OP128);
+        for (int t = 0; t < (s.split ? s.n_t32 : s.n_tiles); ++t) items[ph_op].push_back({b, t});
         // a star with scattering runs its transfer and reverse transfer in launches of its own
         for (int k = 0; k < (s.N + 511) / 512; ++k) {
             if (!s.scatter) items[PH_FLUX].push_back({b, k});
@@ -345,7 +387,7 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
         for (int k = 0; k < s.S + 1; ++k) items[PH_FINAL].push_back({b, k});
     }
     // opacity work: most expensive tiles first (longest-processing-time order)
-    for (int ph : {PH_OP32, PH_OP64, PH_OP128})
+    for (int ph : {PH_OP32, PH_OP64, PH_OP128, PH_SPLIT})
         std::stable_sort(items[ph].begin(), items[ph].end(), [&](const int2& x, const int2& y) {
             return stars[x.x].plan->tile_cost[x.y] > stars[y.x].plan->tile_cost[y.y];
         });
@@ -438,6 +480,10 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
     kb_pop<<<grid(bt->grid512, n[PH_POP]), 512, 0, st>>>(bt->stars, it[PH_POP], n[PH_POP]);
     if (n[PH_LINES]) kb_lines<<<grid(bt->grid512, n[PH_LINES]), 512, 0, st>>>(bt->stars, it[PH_LINES], n[PH_LINES]);
     kb_params<<<grid(bt->grid512, n[PH_PARAMS]), 512, 0, st>>>(bt->stars, it[PH_PARAMS], n[PH_PARAMS]);
+    if (n[PH_SPLIT]) {
+        kb_opacity_far<<<n[PH_SPLIT], FAR_WAVES * WAVE, 0, st>>>(bt->stars, it[PH_SPLIT]);
+        kb_opacity_near<<<dim3(n[PH_SPLIT], near_parts(bt->max_d)), 256, 0, st>>>(bt->stars, it[PH_SPLIT]);
+    }
     if (bt->any_center)
         batch_opacity<true>(bt, st);
     else

@@ -89,6 +89,14 @@ struct StarDev {
     float* xlim;                 // [L] centre test: largest |x| any depth of the line reaches (0: none)
     int* wide_a;                 // [L] 1 if the line's damping ratio spans the near and far wing tiers
     int* wide_any;               // [1] nonzero if any line is flagged (reset by the populations stage)
+    // near/far split of the line sums (pz_split.h); its plans use xfar in wide_a's place
+    bool split;
+    float* xfar;                 // [L] |x| limit of a line's near zone, +inf or -1
+    double window_cm;            // W
+    int n_t32;                   // 32-pixel tiles
+    const int* t32_first;        // [n_t32] lines overlapping each tile: [first, last)
+    const int* t32_last;
+    const int* t32_order;        // tiles by decreasing cost
     double* inv_kcl;             // [L] centre test: 1 / kappa_c at the line centre
     double center_eta;           // centre-test threshold (0: plain windowed sum)
     bool center;
@@ -104,6 +112,7 @@ struct StarDev {
     int grid_opacity;
 };
 
+static constexpr int TILE = 32;          // pixels of a tile of the split sums
 static constexpr int RCHUNK = 2048;      // lines per reduction partial
 static constexpr int SC_WS_ARRAYS = 45;  // [D][Npad] float64 arrays of the scattering workspace
 static constexpr int MAX_CHUNK = 16;     // most lines per LDS chunk of the opacity tile
@@ -158,7 +167,12 @@ struct pz_plan {
     int* tile_order;     // [n_tiles] tiles by decreasing cost (opacity work queue)
     int* qctr;           // [1] opacity work-queue counter
     int grid_opacity;    // persistent opacity workgroups (CUs x occupancy)
-    int64_t* tile_cost;  // host [n_tiles]: Voigt evaluations per opacity tile
+    int64_t* tile_cost;  // host [n_tiles or n_t32]: Voigt evaluations per opacity tile
+    bool split;          // the line sums are split by detuning (pz_split.h)
+    int n_t32;
+    int* t32_first;
+    int* t32_last;
+    int* t32_order;
     void* base;          // single device allocation holding everything above
     // stage profiling (see pz_plan_profile)
     bool prof;

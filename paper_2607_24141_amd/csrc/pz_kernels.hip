@@ -14,8 +14,8 @@ __global__ __launch_bounds__(256) void k_populations(StarDev s) {
 }
 
 __global__ __launch_bounds__(256) void k_line_consts(StarDev s) {
-    __shared__ double red[3 * 256];
-    const double3 bnd = damp_bounds(s, red);
+    __shared__ double red[4 * 256];
+    const DampBounds bnd = damp_bounds(s, red);
     dev_line_consts(s, blockIdx.x * blockDim.x + threadIdx.x, bnd);
 }
 
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void k_opacity(StarDev s
         const int it = __builtin_amdgcn_readfirstlane(s_it);
         __syncthreads();
         if (it >= s.n_tiles) return;
-        dev_opacity_tile<WPX, false, CT, G, true, FG>(s, s.tile_order[it], chunk, sm);
+        dev_opacity_tile<WPX, false, CT, G, true, FG>(s, s.tile_order[it], 0, chunk, sm);
     }
 }
 
@@ -52,7 +52,25 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void k_opacity_wide(Star
     load_pw_table(sm.pw, false);
     __syncthreads();
     for (int t = blockIdx.x; t < s.n_tiles; t += gridDim.x)
-        dev_opacity_tile<WPX, true, CT, opacity_max_groups<WPX>(), true>(s, t, chunk, sm);
+        dev_opacity_tile<WPX, true, CT, opacity_max_groups<WPX>(), true>(s, t, 0, chunk, sm);
+}
+
+// Split sums: one workgroup per 32-pixel tile, dispatched in order of
+// decreasing cost (longest first: tiles differ several-fold in line count).
+__global__ __launch_bounds__(FAR_WAVES * WAVE) void k_opacity_far(StarDev s) {
+    __shared__ FarLds lds;
+    dev_opacity_far(s, s.t32_order[blockIdx.x], lds);
+}
+
+// blockIdx.y: the depth groups NEAR_G y .. of the tile; CT: the plan uses the centre test.
+template <bool CT>
+__global__ __launch_bounds__(256) void k_opacity_near(StarDev s) {
+    __shared__ float4 near_tab[PZ_NEAR_N];
+    __shared__ float4 pw[PZ_PW_LDS];
+    load_near_table(near_tab);
+    load_pw_table(pw, false);
+    __syncthreads();
+    dev_opacity_near<NEAR_G, CT>(s, s.t32_order[blockIdx.x], blockIdx.y, near_tab, pw);
 }
 
 __global__ void k_reset_queue(int* ctr) { ctr[0] = 0; }
@@ -258,6 +276,15 @@ static hipError_t launch_opacity_tiles(const StarDev& s, int chunk, int grid, hi
 
 hipError_t launch_opacity(const StarDev& s, int chunk, hipStream_t st) {
     if (s.n_tiles == 0) return hipSuccess;
+    if (s.split) {
+        k_opacity_far<<<s.n_t32, FAR_WAVES * WAVE, 0, st>>>(s);
+        const dim3 grid(s.n_t32, near_parts(s.D));
+        if (s.center)
+            k_opacity_near<true><<<grid, 256, 0, st>>>(s);
+        else
+            k_opacity_near<false><<<grid, 256, 0, st>>>(s);
+        return hipGetLastError();
+    }
     const int grid = std::max(1, std::min(s.grid_opacity, s.n_tiles));
     k_reset_queue<<<1, 1, 0, st>>>(s.qctr);
     return s.center ? launch_opacity_tiles<true>(s, chunk, grid, st) : launch_opacity_tiles<false>(s, chunk, grid, st);

@@ -99,6 +99,7 @@ extern "C" int synth_forward_noalloc(const pz_plan* plan, const pz_atmos* atm, c
     s.inv_dv = reinterpret_cast<double*>(base + o_idv);
     s.lc = reinterpret_cast<double4*>(base + o_lc);
     s.wide_a = reinterpret_cast<int*>(base + o_wide);
+    s.xfar = reinterpret_cast<float*>(base + o_wide);
     s.wide_any = reinterpret_cast<int*>(base + o_wany);
     s.qctr = reinterpret_cast<int*>(base + o_qctr);
     s.lp = reinterpret_cast<float4*>(base + o_lp);

@@ -108,10 +108,10 @@ __device__ __forceinline__ int scalar_opaque(int x) {
 // consecutive LDS slots; they are complete once the issuing wavefront's load
 // counter drains.  The per-lane byte offsets fit 32 bits: the plan keeps
 // every tile's rows under 2^28 elements.
-template <int WPX, bool CT, class Lds>
+template <int WPX, bool CT, int NTH, class Lds>
 __device__ __forceinline__ void stage_rows(const StarDev& s, int l0, int c, int nch, int nc, float4* dst,
                                            const Lds& sm) {
-    constexpr int LPT = (MAX_CHUNK * MAXD + 511) / 512;
+    constexpr int LPT = (MAX_CHUNK * MAXD + NTH - 1) / NTH;
     const size_t row0 = (size_t)(l0 + c) * s.D;
     // offsets are recomputed per chunk, never hoisted
     const int D = scalar_opaque(s.D), stride = scalar_opaque((nch - 1) * s.D);
@@ -122,7 +122,7 @@ __device__ __forceinline__ void stage_rows(const StarDev& s, int l0, int c, int 
     const char* zm = CT ? scalar_base(s.zmax + row0) : nullptr;
 #pragma unroll
     for (int u = 0; u < LPT; ++u) {
-        const int k0 = u * 512 + (threadIdx.x & ~(WAVE - 1));   // wavefront-uniform
+        const int k0 = u * NTH + (threadIdx.x & ~(WAVE - 1));   // wavefront-uniform
         const int k = k0 + lane;
         if (k0 < n && k < n) {
             // k / D: (k + 1/2) / D lies at least 1/(2D) from an integer
@@ -158,20 +158,20 @@ __device__ __forceinline__ void stage_fields(const StarDev& s, int l0, int c, in
 
 // The window fields of a thread's staged (line, pixel) pairs, loaded before
 // a chunk is summed and turned into detunings after.
-template <int WPX>
+template <int WPX, int NTH>
 struct XFields {
-    static constexpr int XPT = (MAX_CHUNK * 8 * WPX + 511) / 512;
+    static constexpr int XPT = (MAX_CHUNK * 8 * WPX + NTH - 1) / NTH;
     int lo[XPT], hi[XPT], ic[XPT], wide[XPT];
     float dl[XPT];
 };
 
-template <int WPX>
+template <int WPX, int NTH>
 __device__ __forceinline__ void load_xfields(const StarDev& s, int l0, int c, int nch, int nc, bool any_wide,
-                                             XFields<WPX>& f) {
+                                             XFields<WPX, NTH>& f) {
     constexpr int TPX = 8 * WPX;
 #pragma unroll
-    for (int u = 0; u < XFields<WPX>::XPT; ++u) {
-        const int k = threadIdx.x + u * 512;
+    for (int u = 0; u < XFields<WPX, NTH>::XPT; ++u) {
+        const int k = threadIdx.x + u * NTH;
         const int l = l0 + c + min(k / TPX, nc - 1) * nch;
         f.lo[u] = s.ln.ilo[l];
         f.hi[u] = s.ln.ihi[l];
@@ -183,13 +183,13 @@ __device__ __forceinline__ void load_xfields(const StarDev& s, int l0, int c, in
 
 // A line the pass does not take (WIDE: the lines flagged wide_a; else the
 // others) gets kNoLine at every pixel.
-template <int WPX, bool WIDE>
+template <int WPX, bool WIDE, int NTH>
 __device__ __forceinline__ void write_x_lds(const StarDev& s, int nc, int p0, bool any_wide, const int* fl,
                                             float* dst) {
     constexpr int TPX = 8 * WPX;
 #pragma unroll
-    for (int u = 0; u < XFields<WPX>::XPT; ++u) {
-        const int k = threadIdx.x + u * 512;
+    for (int u = 0; u < XFields<WPX, NTH>::XPT; ++u) {
+        const int k = threadIdx.x + u * NTH;
         if (k < nc * TPX) {
             const int q = k / TPX, i = p0 + (k - q * TPX);
             const int lo = fl[q], hi = fl[MAX_CHUNK + q], ic = fl[2 * MAX_CHUNK + q];
@@ -202,13 +202,13 @@ __device__ __forceinline__ void write_x_lds(const StarDev& s, int nc, int p0, bo
     }
 }
 
-template <int WPX, bool CT, bool WIDE>
+template <int WPX, bool CT, bool WIDE, int NTH>
 __device__ __forceinline__ void write_x(const StarDev& s, int l0, int c, int nch, int nc, int p0, float* dst,
-                                        const XFields<WPX>& f) {
+                                        const XFields<WPX, NTH>& f) {
     constexpr int TPX = 8 * WPX;
 #pragma unroll
-    for (int u = 0; u < XFields<WPX>::XPT; ++u) {
-        const int k = threadIdx.x + u * 512;
+    for (int u = 0; u < XFields<WPX, NTH>::XPT; ++u) {
+        const int k = threadIdx.x + u * NTH;
         if (k < nc * TPX) {
             const int q = k / TPX, i = p0 + (k - q * TPX);
             float x = kNoLine;
@@ -244,13 +244,13 @@ __device__ __forceinline__ void wing_sums(float* acc, const float4* pd, const fl
 template <int WPX>
 constexpr int opacity_max_groups() { return MAXD / (64 / WPX); }
 
-template <int WPX, bool CT, bool WIDE, int G, bool PAIRED, bool FG, class Lds>
-__device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, int chunk, const Lds& sm) {
+template <int WPX, bool CT, bool WIDE, int G, bool PAIRED, bool FG, int NTH, class Lds>
+__device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, int sub, int chunk, const Lds& sm) {
     constexpr int NDG = 64 / WPX;
     constexpr int DPT = G;                             // depth-group slots (>= full groups)
     static_assert(G >= 1 && G <= MAXD / NDG, "depth-group slots");
     constexpr int TPX = 8 * WPX;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x + sub * NTH;          // the thread's place in the whole tile
     const int lane = tid % 64;
     const int wave = tid / 64;
     const int px = wave * WPX + lane % WPX;           // main pixel within the tile
@@ -269,7 +269,7 @@ __device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, in
     if (WIDE && !any_wide) return;
     if (WIDE) {                                        // nothing to add unless a line of the tile is flagged
         int any = 0;
-        for (int l = l0 + tid; l < l1; l += 512) any |= s.wide_a[l];
+        for (int l = l0 + threadIdx.x; l < l1; l += NTH) any |= s.wide_a[l];
         if (!__syncthreads_or(any)) return;
     }
     float acc[DPT], acc_t = 0.0f;
@@ -283,7 +283,7 @@ __device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, in
     auto lines_in = [&](int c) { return per_chunk + (c < extra ? 1 : 0); };
     constexpr bool DB = Lds::NB == 2;                  // double-buffered chunks
     static_assert(!CT || !DB, "the centre test stages one buffer");
-    XFields<WPX> f;
+    XFields<WPX, NTH> f;
     // Sums chunk c from (rows, xs).  DB: first starts the copies of chunk
     // c + 1's rows into nrows; PAIRED, also of chunk c + 2's window fields
     // into fcur, and after the sum chunk c + 1's detunings go to nxs from
@@ -294,17 +294,17 @@ __device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, in
         const int nc = lines_in(c);
         const bool more = DB && c + 1 < nch;
         if (!DB) {                                     // one buffer: stage, then sum
-            stage_rows<WPX, CT>(s, l0, c, nch, nc, sm.lp0, sm);
-            load_xfields<WPX>(s, l0, c, nch, nc, any_wide, f);
-            write_x<WPX, CT, WIDE>(s, l0, c, nch, nc, p0, sm.x0, f);
+            stage_rows<WPX, CT, NTH>(s, l0, c, nch, nc, sm.lp0, sm);
+            load_xfields<WPX, NTH>(s, l0, c, nch, nc, any_wide, f);
+            write_x<WPX, CT, WIDE, NTH>(s, l0, c, nch, nc, p0, sm.x0, f);
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         } else if (PAIRED) {
-            if (more) stage_rows<WPX, CT>(s, l0, c + 1, nch, lines_in(c + 1), nrows, sm);
+            if (more) stage_rows<WPX, CT, NTH>(s, l0, c + 1, nch, lines_in(c + 1), nrows, sm);
             if (c + 2 < nch) stage_fields(s, l0, c + 2, nch, lines_in(c + 2), fcur);
         } else if (more) {
-            stage_rows<WPX, CT>(s, l0, c + 1, nch, lines_in(c + 1), nrows, sm);
-            load_xfields<WPX>(s, l0, c + 1, nch, lines_in(c + 1), any_wide, f);
+            stage_rows<WPX, CT, NTH>(s, l0, c + 1, nch, lines_in(c + 1), nrows, sm);
+            load_xfields<WPX, NTH>(s, l0, c + 1, nch, lines_in(c + 1), any_wide, f);
         }
         for (int q = 0; q < nc; ++q) {
             const float4* row = rows + q * D;
@@ -353,19 +353,19 @@ __device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, in
         }
         if (more) {
             if (PAIRED)
-                write_x_lds<WPX, WIDE>(s, lines_in(c + 1), p0, any_wide, fnext, nxs);
+                write_x_lds<WPX, WIDE, NTH>(s, lines_in(c + 1), p0, any_wide, fnext, nxs);
             else
-                write_x<WPX, CT, WIDE>(s, l0, c + 1, nch, lines_in(c + 1), p0, nxs, f);
+                write_x<WPX, CT, WIDE, NTH>(s, l0, c + 1, nch, lines_in(c + 1), p0, nxs, f);
         }
         if (DB) __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     };
     if (DB) {
         if (nch > 0) {
-            stage_rows<WPX, CT>(s, l0, 0, nch, lines_in(0), sm.lp0, sm);
+            stage_rows<WPX, CT, NTH>(s, l0, 0, nch, lines_in(0), sm.lp0, sm);
             if (PAIRED && nch > 1) stage_fields(s, l0, 1, nch, lines_in(1), sm.f1);
-            load_xfields<WPX>(s, l0, 0, nch, lines_in(0), any_wide, f);
-            write_x<WPX, CT, WIDE>(s, l0, 0, nch, lines_in(0), p0, sm.x0, f);
+            load_xfields<WPX, NTH>(s, l0, 0, nch, lines_in(0), any_wide, f);
+            write_x<WPX, CT, WIDE, NTH>(s, l0, 0, nch, lines_in(0), p0, sm.x0, f);
         }
         __builtin_amdgcn_s_waitcnt(0);                // the LDS copies count as loads
         __syncthreads();
@@ -404,7 +404,9 @@ __device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, in
     }
 }
 
-// Called by all 512 threads of a workgroup (it synchronises the workgroup);
+// Called by all NTH threads of a workgroup (it synchronises the workgroup):
+// the whole tile (512), or one of the 512 / NTH parts of its wavefronts (sub),
+// which stages every line of the tile for its own wavefronts alone;
 // sm.pw must hold the piecewise core table.  The main pass (WIDE = false)
 // writes the tile's opacity from every line not flagged wide_a; the wide
 // pass then adds the flagged lines (whose damping ratio spans both near and
@@ -415,12 +417,12 @@ __device__ __forceinline__ void opacity_tile_body(const StarDev& s, int tile, in
 // PAIRED: the plain sum runs its chunks in statically paired buffers (faster
 // where the registers allow, as in the single-star kernels; the batch
 // kernels, which also hold their work queue's state, take the one-body loop).
-template <int WPX, bool WIDE, bool ANYCT, int G, bool PAIRED, bool FG = false>
-__device__ __forceinline__ void dev_opacity_tile(const StarDev& s, int tile, int chunk, const OpacityLds<WPX, ANYCT>& sm) {
+template <int WPX, bool WIDE, bool ANYCT, int G, bool PAIRED, bool FG = false, int NTH = 512>
+__device__ __forceinline__ void dev_opacity_tile(const StarDev& s, int tile, int sub, int chunk, const OpacityLds<WPX, ANYCT>& sm) {
     if (ANYCT && s.center)
-        opacity_tile_body<WPX, ANYCT, WIDE, G, PAIRED, FG>(s, tile, chunk, sm);
+        opacity_tile_body<WPX, ANYCT, WIDE, G, PAIRED, FG, NTH>(s, tile, sub, chunk, sm);
     else
-        opacity_tile_body<WPX, false, WIDE, G, PAIRED, FG>(s, tile, chunk, sm);
+        opacity_tile_body<WPX, false, WIDE, G, PAIRED, FG, NTH>(s, tile, sub, chunk, sm);
 }
 
 }  // namespace pz

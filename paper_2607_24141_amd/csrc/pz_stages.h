@@ -85,34 +85,47 @@ __device__ __forceinline__ void dev_select(const StarDev& s, int l, double eta, 
 // Per line (Eqs. 4, 5, 30), in float64:
 //   x = (pi e^2/m_e c) 10^(loggf+dgf) lambda_l / sqrt(pi)
 //   y, z, w = 10^ddamp lambda_l / (4 pi) x (g_rad 10^d_rad, g_S 10^d_S, g_vdW 10^d_vdW)
-// Block-wide maxima of n_e and n_pert over depth and of 1/dv over (species,
-// depth): with them (g_rad + g_S max n_e + g_vdW max n_pert) max(1/dv) bounds
-// every line's damping ratio a from above.  Every thread of the workgroup
-// calls this (it synchronises); red holds 3 doubles per thread.
-__device__ __forceinline__ double3 damp_bounds(const StarDev& s, double* red) {
+// Block-wide maxima of n_e, n_pert and T over depth and of 1/dv over (species,
+// depth).  They bound every line's damping width, damping ratio and Doppler
+// width over depth.  Every thread of the workgroup calls this (it
+// synchronises); red holds 4 doubles per thread.
+struct DampBounds {
+    double ne, npert, inv_dv, T;
+};
+
+__device__ __forceinline__ DampBounds damp_bounds(const StarDev& s, double* red) {
     const int t = threadIdx.x, n = blockDim.x;
-    double a = 0.0, b = 0.0, c = 0.0;
+    double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
     for (int j = t; j < s.D; j += n) {
         a = fmax(a, s.ne[j]);
         b = fmax(b, s.npert[j]);
+        d = fmax(d, s.T[j]);
     }
     for (int k = t; k < s.S * s.D; k += n) c = fmax(c, s.inv_dv[k]);
     red[t] = a;
     red[n + t] = b;
     red[2 * n + t] = c;
+    red[3 * n + t] = d;
     __syncthreads();
     for (int w = n / 2; w > 0; w >>= 1) {
         if (t < w)
-            for (int r = 0; r < 3; ++r) red[r * n + t] = fmax(red[r * n + t], red[r * n + t + w]);
+            for (int r = 0; r < 4; ++r) red[r * n + t] = fmax(red[r * n + t], red[r * n + t + w]);
         __syncthreads();
     }
-    const double3 out = make_double3(red[0], red[n], red[2 * n]);
+    const DampBounds out = {red[0], red[n], red[2 * n], red[3 * n]};
     __syncthreads();
     return out;
 }
 
+// No pixel of a line's window has |x| above this: |lambda_l / lambda_i - 1| <=
+// W / lambda_i <= W / (lambda_l - W), with room for rounding.
+__device__ __forceinline__ float window_reach(const StarDev& s, double lam_cm) {
+    const double den = lam_cm - s.window_cm;
+    return den > 0.0 ? (float)(s.window_cm / den * (1.0 + 1.0e-4) + 1.0e-6) : INFINITY;
+}
+
 // bnd: damp_bounds of the workgroup.
-__device__ __forceinline__ void dev_line_consts(const StarDev& s, int l, double3 bnd) {
+__device__ __forceinline__ void dev_line_consts(const StarDev& s, int l, const DampBounds& bnd) {
     if (l >= s.L) return;
     const int caller = s.ln.perm[l];
     const double lam = s.ln.lam_cm[l];
@@ -120,23 +133,33 @@ __device__ __forceinline__ void dev_line_consts(const StarDev& s, int l, double3
     const double line_const = PI * E_CHARGE * E_CHARGE / (M_ELECTRON * C_LIGHT);
     const double damp = (s.ddamp ? exp10((double)s.ddamp[caller]) : 1.0) * lam / (4.0 * PI);
     const float* df = s.ddamp_family;                    // per-family corrections, [3][L] caller order
-    s.lc[l] = make_double4(line_const * exp10(loggf) * lam / sqrt(PI),
-                           damp * exp10(s.ln.lgr[l] + (df ? (double)df[caller] : 0.0)),
-                           damp * exp10(s.ln.lgs[l] + (df ? (double)df[s.L + caller] : 0.0)),
-                           damp * exp10(s.ln.lgw[l] + (df ? (double)df[2 * s.L + caller] : 0.0)));
-    {   // damping-ratio range over depth: flags lines whose wavefronts can mix near and far wing tiers
-        const double4 c = s.lc[l];
-        bool wide = false;
-        if (fma(c.w, bnd.y, fma(c.z, bnd.x, c.y)) * bnd.z > 1.0e3) {   // else a <= 1000 at every depth
-            const int sp = s.ln.spion[l] >> 1;
-            double amin = 1e300, amax = 0.0;
-            for (int j = 0; j < s.D; ++j) {
-                const double a = fma(c.w, s.npert[j], fma(c.z, s.ne[j], c.y)) * s.inv_dv[sp * s.D + j];
-                amin = fmin(amin, a);
-                amax = fmax(amax, a);
-            }
-            wide = (amin < 8.0 && amax > 1.0e3) || (amin < 40.0 && amax > 3.0e4);
+    const double4 c = make_double4(line_const * exp10(loggf) * lam / sqrt(PI),
+                                   damp * exp10(s.ln.lgr[l] + (df ? (double)df[caller] : 0.0)),
+                                   damp * exp10(s.ln.lgs[l] + (df ? (double)df[s.L + caller] : 0.0)),
+                                   damp * exp10(s.ln.lgw[l] + (df ? (double)df[2 * s.L + caller] : 0.0)));
+    s.lc[l] = c;
+    const int sp = s.ln.spion[l] >> 1;
+    const double gam = fma(c.w, bnd.npert, fma(c.z, bnd.ne, c.y));           // >= a dv at every depth
+    // damping-ratio range over depth: flags lines whose wavefronts can mix near and far wing tiers
+    bool wide = false;
+    if (gam * bnd.inv_dv > 1.0e3) {                        // else a <= 1000 at every depth
+        double amin = 1e300, amax = 0.0;
+        for (int j = 0; j < s.D; ++j) {
+            const double a = fma(c.w, s.npert[j], fma(c.z, s.ne[j], c.y)) * s.inv_dv[sp * s.D + j];
+            amin = fmin(amin, a);
+            amax = fmax(amax, a);
         }
+        wide = (amin < 8.0 && amax > 1.0e3) || (amin < 40.0 && amax > 3.0e4);
+    }
+    if (s.split) {
+        // Far zone: v = x c / dv >= FAR_V at the widest dv, and a <= FAR_AV v,
+        // i.e. x >= (a dv / c) / FAR_AV, at the largest damping width.
+        const double xi = (double)s.xi[0] * 1.0e5;
+        const double dv = sqrt(2.0 * K_BOLTZ * bnd.T / (s.mass[sp] * AMU_G) + xi * xi);
+        float xfar = (float)(fmax(PZ_FAR_V * dv, gam / PZ_FAR_AV) / C_LIGHT * (1.0 + 1.0e-6));
+        if (!(xfar < window_reach(s, lam))) xfar = INFINITY;   // no far pixel in the window (or not a number)
+        s.xfar[l] = wide ? -1.0f : xfar;
+    } else {
         s.wide_a[l] = wide ? 1 : 0;
         if (wide) atomicOr(s.wide_any, 1);
     }
@@ -168,7 +191,10 @@ __device__ __forceinline__ void dev_line_params(const StarDev& s, long idx) {
     const double ikT = 1.0 / (K_BOLTZ * T);
     const double K = c.x * s.pop[spion * s.D + j] * exp(-s.ln.E_eV[l] * EV_ERG * ikT) *
                      (-expm1(-(H_PLANCK * C_LIGHT) / s.ln.lam_cm[l] * ikT)) * inv_dv;
-    if (valid) s.lp[idx] = make_float4((float)(C_LIGHT * inv_dv), (float)(a * a), (float)K, (float)(K * a));
+    const float4 q = make_float4((float)(C_LIGHT * inv_dv), (float)(a * a), (float)K, (float)(K * a));
+    if (valid) s.lp[idx] = q;
+    // a row that is not finite stays with the pixels of its own window: no far zone
+    if (s.split && valid && !(fabsf(q.x) + q.y + fabsf(q.z) + fabsf(q.w) < INFINITY) && s.xfar[l] >= 0.0f) s.xfar[l] = INFINITY;
     if (!s.center) return;
     // continuum-referenced centre test, decided in float64: keep iff
     // K H(a,0) >= eta kappa_c(lambda_l); a kept pair deposits where
@@ -183,6 +209,8 @@ __device__ __forceinline__ void dev_line_params(const StarDev& s, long idx) {
         xl = (float)(V / (C_LIGHT * inv_dv));              // detuning |x| = V dv / c
     }
     if (valid) s.zmax[idx] = zm;
+    // a span that ends inside the window is cut pixel by pixel: no far zone
+    if (s.split && valid && !(xl > window_reach(s, s.ln.lam_cm[l])) && s.xfar[l] >= 0.0f) s.xfar[l] = INFINITY;
     // Largest |x| over each line's depths: one wavefront-wide max and one
     // atomic per distinct line in the wavefront (non-negative floats order as
     // their bit patterns; the result does not depend on the order).
@@ -203,6 +231,7 @@ __device__ __forceinline__ void dev_line_params(const StarDev& s, long idx) {
 }  // namespace pz
 
 #include "pz_opacity.h"
+#include "pz_split.h"
 
 namespace pz {
 

@@ -208,6 +208,68 @@ __device__ __forceinline__ bool wave_all(bool c) {
 }
 __device__ __forceinline__ bool wave_any(bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; }
 
+// ------------------------------------------------------ near and far zones
+// The sums over a line's window are split by detuning (see pz_opacity.h).
+// Near zone, a <= 0.15 and v^2 < PZ_NEAR_V^2, one formula without regions:
+// with g = (2/sqrt(pi)) (2 v F(v) - 1), F Dawson's integral, and s = 2/sqrt(pi),
+//   H = exp(a^2-u) cos(2av) + a [g + a^2 (s/3 + g (1 - 2u/3))
+//       + a^4 (s (7/30 - u/15) + g (1/2 - 2u/3 + 2u^2/15))],
+// the a^3 and a^5 terms by the recurrence of F's derivatives; what they lose
+// to cancellation (~1e-7 of s, at weights a^2 <= 0.0225 and a^4) stays below
+// 4e-8 of H.  g is piecewise cubic in |v|, one 16-byte LDS read per
+// evaluation (the piecewise core tables take three or four).  H within
+// 1.2e-6 of w(z), float32 exp included; rms 1e-7.
+static constexpr float kNearS = 1.1283791671f;
+
+// 16 v exactly splits |v| into the interval and its fraction.
+__device__ __forceinline__ float near_g(float v, const float4* tab) {
+    const float x = fabsf(v) * PZ_NEAR_INV;
+    const float4 q = tab[(int)x];
+    const float r = __builtin_amdgcn_fractf(x);
+    return fmaf(fmaf(fmaf(q.w, r, q.z), r, q.y), r, q.x);
+}
+
+__device__ __forceinline__ void load_near_table(float4* dst) {
+    float* d = reinterpret_cast<float*>(dst);
+    for (int k = threadIdx.x; k < 4 * PZ_NEAR_N; k += blockDim.x) d[k] = PZ_NEAR_TAB[k];
+}
+
+// acc + K H on the near zone; FULL adds the a^5 term (needed above a = 0.03).
+template <bool FULL>
+__device__ __forceinline__ float near_KH_acc(float acc, float a2, float K, float Ka, float v, const float4* tab) {
+    const float u = v * v;
+    const float g = near_g(v, tab);
+    float d = fmaf(g, fmaf(-2.0f / 3.0f, u, 1.0f), kNearS / 3.0f);
+    if (FULL) {
+        const float p = fmaf(fmaf(2.0f / 15.0f, u, -2.0f / 3.0f), u, 0.5f);
+        d = fmaf(a2, fmaf(g, p, fmaf(-kNearS / 15.0f, u, kNearS * 7.0f / 30.0f)), d);
+    }
+    const float lam = fmaf(a2, d, g);
+    const float y = a2 * u;                             // (2av)^2 / 4
+    const float cs = fmaf(fmaf(fmaf(fmaf(2.0f / 315.0f, y, -4.0f / 45.0f), y, 2.0f / 3.0f), y, -2.0f), y, 1.0f);
+    return fmaf(Ka, lam, fmaf(K * __expf(a2 - u), cs, acc));
+}
+
+// Far zone, v >= PZ_FAR_V and a <= PZ_FAR_AV v at every depth of a line: with
+// x0 the line's zone limit and U = (x0/x)^2, w = 1/v^2 = W U, W = 1/(s x0)^2,
+//   K H = sum_n C_n U^n,  C_n = (K a/sqrt(pi)) W^n P_(n-1)(a^2),  n = 1..PZ_FAR_N:
+// a product of a (pixel, line) and a (line, depth) factor for each n.
+// Coefficients P_n(b) W^n of one set (T: the triangle of ascending powers).
+template <int NT>
+__device__ __forceinline__ void far_poly(const float* T, float b, float W, float lead, float* C) {
+    float wn = lead;
+    int o = 0;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+        float p = T[o + n];
+#pragma unroll
+        for (int k = n - 1; k >= 0; --k) p = fmaf(p, b, T[o + k]);
+        C[n] = wn * p;
+        wn *= W;
+        o += n + 1;
+    }
+}
+
 // Line-depth parameters arrive as (a^2, K, K a) with K the line-strength
 // factor; the functions return K-scaled results.  Every branch on __any /
 // __all is wavefront-uniform; the tests run in order of how often each tier
