@@ -106,6 +106,15 @@ bool split_rule(int N, int L, int D, int64_t evals) {
     return window_px >= 165.0 || per_px <= 5.5;
 }
 
+// Whether the gather of a split plan is split too (pz_split_gather.h).  With
+// the centre test most lines of a dense catalogue are cut inside their window
+// at some depth, have no far zone and are summed directly either way: at 4.8
+// lines per pixel (120,000 lines, 1560-1700 nm) the split gather takes 0.98 ms
+// and the direct one 1.03, so those plans keep the direct one, with the
+// rounding of its ill-conditioned sums; sparse catalogues, and all plans
+// without the centre test, gain (1500-1700 nm: 1.05 against 1.93 ms).
+bool split_gather_rule(int N, int L, bool center) { return !center || L <= N; }
+
 }  // namespace
 
 extern "C" {
@@ -345,6 +354,7 @@ int pz_plan_create(const pz_grid* grid, const pz_lines* lines, int32_t n_species
     p->tile_order = (int*)(base + o_order);
     p->qctr = (int*)(base + o_qctr);
     p->split = split;
+    p->split_gather = split && split_gather_rule(N, L, opts->center_eta > 0.0);
     p->n_t32 = n_t32;
     p->t32_first = (int*)(base + o_t32f);
     p->t32_last = (int*)(base + o_t32l);
@@ -548,6 +558,7 @@ StarDev make_star(const pz_plan* p, const pz_atmos* atm, const pz_params* par) {
     s.wide_a = p->wide_a;
     s.wide_any = p->wide_any;
     s.split = p->split;
+    s.split_gather = p->split_gather;
     s.xfar = reinterpret_cast<float*>(p->wide_a);
     s.window_cm = p->window_nm * 1.0e-7;
     s.n_t32 = p->n_t32;

@@ -33,11 +33,14 @@ enum Phase {
     PH_OP64,       // ... 64-pixel tiles
     PH_OP128,      // ... 128-pixel tiles
     PH_SPLIT,      // (star, 32-pixel tile) of stars with split sums, decreasing cost
+    PH_FAR2,       // (star, 32-pixel tile): far zone of stars with short grids
+    PH_FAR4,       // (star, 64-pixel tile): ... with long ones
     PH_FLUX,       // (star, 512 pixels)
     PH_SEED,       // (star, 512 pixels): chi^2 seed for stars with a target
     PH_LOSS,       // (star): chi^2 value, one 1024-thread workgroup
     PH_REVERSE,    // (star, 64 pixels), 64-thread workgroups
     PH_GATHER,     // (star, GATHER_ITEM lines), atomic queue
+    PH_GSPLIT,     // (star, GATHER_ITEM lines) of stars with split sums
     PH_SCATTER,    // (star, 512 lines)
     PH_PARTIAL,    // (star, list b * n_rchunk + c)
     PH_FINAL,      // (star, list b)
@@ -126,11 +129,18 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void kb_opacity_wide(con
     }
 }
 
-// Split sums: one workgroup per (star, tile) item, dispatched in order of decreasing cost.
-__global__ __launch_bounds__(FAR_WAVES * WAVE) void kb_opacity_far(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
-    __shared__ FarLds lds;
+// Split sums: one workgroup per (star, tile) item; the far zone's form is the
+// one that the star's own calls take.
+__global__ __launch_bounds__(FAR_MAX_WAVES / 2 * WAVE) void kb_opacity_far2(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ FarLds<2> lds;
     const int2 w = uniform_item(items, blockIdx.x);
-    dev_opacity_far(stars[w.x], w.y, lds);
+    dev_opacity_far<2>(stars[w.x], w.y, lds);
+}
+
+__global__ __launch_bounds__(4 * WAVE) void kb_opacity_far4(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ FarLds<4> lds;
+    const int2 w = uniform_item(items, blockIdx.x);
+    dev_opacity_far<4>(stars[w.x], w.y, lds);
 }
 
 // blockIdx.y: the depth groups of the tile (enough for the deepest star).
@@ -221,6 +231,34 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
             dev_gather(s, l, lane, pw, lq[wave]);
         }
     }
+}
+
+// Split sums: GATHER_ITEM lines per workgroup, by two pairs of wavefronts and then one wavefront per line.
+__global__ __launch_bounds__(256) void kb_gather_far(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    const int2 w = uniform_item(items, blockIdx.x);
+    const StarDev& s = stars[w.x];
+    __shared__ LineSums hand[2][GFAR_LINES];
+    const int wave = threadIdx.x / WAVE;
+    for (int q = 0; q < GATHER_ITEM; q += 2 * GFAR_LINES) {
+        const int base = w.y * GATHER_ITEM + q + wave / 2 * GFAR_LINES;
+        if (s.fam)
+            dev_gather_far<true>(s, base, wave % 2, hand[wave / 2]);
+        else
+            dev_gather_far<false>(s, base, wave % 2, hand[wave / 2]);
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(256) void kb_gather_near(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ float4 near_tab[PZ_NEAR_N];
+    __shared__ float4 pw[2 * PZ_PW_LDS];
+    load_near_table(near_tab);
+    load_pw_table(pw, true);
+    __syncthreads();
+    const int2 w = uniform_item(items, blockIdx.x);
+    const StarDev& s = stars[w.x];
+    for (int q = threadIdx.x / WAVE; q < GATHER_ITEM; q += 4)
+        dev_gather_split(s, __builtin_amdgcn_readfirstlane(w.y * GATHER_ITEM + q), threadIdx.x % WAVE, near_tab, pw);
 }
 
 __global__ __launch_bounds__(512) void kb_scatter(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n) {
@@ -373,6 +411,10 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
         for (long k = 0; k < (nld + PARAM_ITEM - 1) / PARAM_ITEM; ++k) items[PH_PARAMS].push_back({b, (int)k});
         const int ph_op = s.split ? PH_SPLIT : s.tile_px == 32 ? PH_OP32 : (s.tile_px == 64 ? PH_OP64 : PH_OP128);
         for (int t = 0; t < (s.split ? s.n_t32 : s.n_tiles); ++t) items[ph_op].push_back({b, t});
+        if (s.split) {
+            const bool wide = far_wide(s.n_t32);
+            for (int t = 0; t < (wide ? (s.n_t32 + 1) / 2 : s.n_t32); ++t) items[wide ? PH_FAR4 : PH_FAR2].push_back({b, t});
+        }
         // a star with scattering runs its transfer and reverse transfer in launches of its own
         for (int k = 0; k < (s.N + 511) / 512; ++k) {
             if (!s.scatter) items[PH_FLUX].push_back({b, k});
@@ -381,7 +423,7 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
         if (!s.scatter)
             for (int k = 0; k < (s.N + 63) / 64; ++k) items[PH_REVERSE].push_back({b, k});
         if (st.y && st.loss) items[PH_LOSS].push_back({b, 0});
-        for (int k = 0; k < (s.L + GATHER_ITEM - 1) / GATHER_ITEM; ++k) items[PH_GATHER].push_back({b, k});
+        for (int k = 0; k < (s.L + GATHER_ITEM - 1) / GATHER_ITEM; ++k) items[s.split_gather ? PH_GSPLIT : PH_GATHER].push_back({b, k});
         for (int k = 0; k < (s.L + 511) / 512; ++k) items[PH_SCATTER].push_back({b, k});
         for (int k = 0; k < (s.S + 1) * s.n_rchunk; ++k) items[PH_PARTIAL].push_back({b, k});
         for (int k = 0; k < s.S + 1; ++k) items[PH_FINAL].push_back({b, k});
@@ -481,7 +523,8 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
     if (n[PH_LINES]) kb_lines<<<grid(bt->grid512, n[PH_LINES]), 512, 0, st>>>(bt->stars, it[PH_LINES], n[PH_LINES]);
     kb_params<<<grid(bt->grid512, n[PH_PARAMS]), 512, 0, st>>>(bt->stars, it[PH_PARAMS], n[PH_PARAMS]);
     if (n[PH_SPLIT]) {
-        kb_opacity_far<<<n[PH_SPLIT], FAR_WAVES * WAVE, 0, st>>>(bt->stars, it[PH_SPLIT]);
+        if (n[PH_FAR4]) kb_opacity_far4<<<n[PH_FAR4], 4 * WAVE, 0, st>>>(bt->stars, it[PH_FAR4]);
+        if (n[PH_FAR2]) kb_opacity_far2<<<n[PH_FAR2], 8 * WAVE, 0, st>>>(bt->stars, it[PH_FAR2]);
         kb_opacity_near<<<dim3(n[PH_SPLIT], near_parts(bt->max_d)), 256, 0, st>>>(bt->stars, it[PH_SPLIT]);
     }
     if (bt->any_center)
@@ -505,8 +548,13 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
             const hipError_t e = launch_reverse_scan(s, st);
             if (e != hipSuccess) return set_error(PZ_E_HIP, hipGetErrorString(e));
         }
-        kb_gather<<<grid(bt->grid_gather, n[PH_GATHER]), 512, 0, st>>>(bt->stars, it[PH_GATHER], n[PH_GATHER],
-                                                                        bt->ctr + 3);
+        if (n[PH_GSPLIT]) {
+            kb_gather_far<<<n[PH_GSPLIT], 256, 0, st>>>(bt->stars, it[PH_GSPLIT]);
+            kb_gather_near<<<n[PH_GSPLIT], 256, 0, st>>>(bt->stars, it[PH_GSPLIT]);
+        }
+        if (n[PH_GATHER])
+            kb_gather<<<grid(bt->grid_gather, n[PH_GATHER]), 512, 0, st>>>(bt->stars, it[PH_GATHER], n[PH_GATHER],
+                                                                            bt->ctr + 3);
         kb_scatter<<<grid(bt->grid512, n[PH_SCATTER]), 512, 0, st>>>(bt->stars, it[PH_SCATTER], n[PH_SCATTER]);
         kb_partial<<<grid(bt->grid256, n[PH_PARTIAL]), 256, 0, st>>>(bt->stars, it[PH_PARTIAL], n[PH_PARTIAL]);
         kb_final<<<grid(bt->grid256, n[PH_FINAL]), 256, 0, st>>>(bt->stars, it[PH_FINAL], n[PH_FINAL]);

@@ -91,6 +91,7 @@ struct StarDev {
     int* wide_any;               // [1] nonzero if any line is flagged (reset by the populations stage)
     // near/far split of the line sums (pz_split.h); its plans use xfar in wide_a's place
     bool split;
+    bool split_gather;           // the gather too (pz_split_gather.h)
     float* xfar;                 // [L] |x| limit of a line's near zone, +inf or -1
     double window_cm;            // W
     int n_t32;                   // 32-pixel tiles
@@ -169,6 +170,7 @@ struct pz_plan {
     int grid_opacity;    // persistent opacity workgroups (CUs x occupancy)
     int64_t* tile_cost;  // host [n_tiles or n_t32]: Voigt evaluations per opacity tile
     bool split;          // the line sums are split by detuning (pz_split.h)
+    bool split_gather;   // and their adjoint (pz_split_gather.h)
     int n_t32;
     int* t32_first;
     int* t32_last;

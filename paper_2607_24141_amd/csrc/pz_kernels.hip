@@ -57,9 +57,10 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void k_opacity_wide(Star
 
 // Split sums: one workgroup per 32-pixel tile, dispatched in order of
 // decreasing cost (longest first: tiles differ several-fold in line count).
-__global__ __launch_bounds__(FAR_WAVES * WAVE) void k_opacity_far(StarDev s) {
-    __shared__ FarLds lds;
-    dev_opacity_far(s, s.t32_order[blockIdx.x], lds);
+template <int NPT>
+__global__ __launch_bounds__(FAR_MAX_WAVES / 2 * WAVE) void k_opacity_far(StarDev s) {
+    __shared__ FarLds<NPT> lds;
+    dev_opacity_far<NPT>(s, NPT == 2 ? s.t32_order[blockIdx.x] : blockIdx.x, lds);
 }
 
 // blockIdx.y: the depth groups NEAR_G y .. of the tile; CT: the plan uses the centre test.
@@ -203,6 +204,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     dev_gather(s, l, threadIdx.x % WAVE, pw, lq[w]);
 }
 
+// Split sums: two pairs of wavefronts with 16 lines each, then one wavefront per line.
+template <bool FAM>
+__global__ __launch_bounds__(256) void k_gather_far(StarDev s) {
+    __shared__ LineSums hand[2][GFAR_LINES];
+    const int blk = xcd_contiguous_block(blockIdx.x, gridDim.x), wave = threadIdx.x / WAVE;
+    dev_gather_far<FAM>(s, (blk * 2 + wave / 2) * GFAR_LINES, wave % 2, hand[wave / 2]);
+}
+
+template <bool CT, bool FAM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_gather_near(StarDev s) {
+    __shared__ float4 near_tab[PZ_NEAR_N];
+    __shared__ float4 pw[2 * PZ_PW_LDS];
+    load_near_table(near_tab);
+    load_pw_table(pw, true);
+    __syncthreads();
+    const int blk = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    const int l = __builtin_amdgcn_readfirstlane(blk * (256 / WAVE) + threadIdx.x / WAVE);
+    if (l < s.L) dev_gather_near<CT, FAM>(s, l, threadIdx.x % WAVE, near_tab, pw);
+}
+
 __global__ __launch_bounds__(256) void k_scatter_lines(StarDev s) { dev_scatter(s, blockIdx.x * blockDim.x + threadIdx.x); }
 
 __global__ __launch_bounds__(256) void k_reduce_partials(StarDev s) {
@@ -277,7 +298,8 @@ static hipError_t launch_opacity_tiles(const StarDev& s, int chunk, int grid, hi
 hipError_t launch_opacity(const StarDev& s, int chunk, hipStream_t st) {
     if (s.n_tiles == 0) return hipSuccess;
     if (s.split) {
-        k_opacity_far<<<s.n_t32, FAR_WAVES * WAVE, 0, st>>>(s);
+        far_wide(s.n_t32) ? k_opacity_far<4><<<(s.n_t32 + 1) / 2, 4 * WAVE, 0, st>>>(s)
+                          : k_opacity_far<2><<<s.n_t32, 8 * WAVE, 0, st>>>(s);
         const dim3 grid(s.n_t32, near_parts(s.D));
         if (s.center)
             k_opacity_near<true><<<grid, 256, 0, st>>>(s);
@@ -312,6 +334,17 @@ hipError_t launch_reverse_scan(const StarDev& s, hipStream_t st) {
 
 hipError_t launch_gather(const StarDev& s, hipStream_t st) {
     if (s.L == 0) return hipSuccess;
+    if (s.split_gather) {
+        const int far = (s.L + 2 * GFAR_LINES - 1) / (2 * GFAR_LINES), near = (s.L + 3) / 4;
+        if (s.fam) {
+            k_gather_far<true><<<far, 256, 0, st>>>(s);
+            s.center ? k_gather_near<true, true><<<near, 256, 0, st>>>(s) : k_gather_near<false, true><<<near, 256, 0, st>>>(s);
+        } else {
+            k_gather_far<false><<<far, 256, 0, st>>>(s);
+            s.center ? k_gather_near<true, false><<<near, 256, 0, st>>>(s) : k_gather_near<false, false><<<near, 256, 0, st>>>(s);
+        }
+        return hipGetLastError();
+    }
     k_gather<<<(s.L + 3) / 4, 256, 0, st>>>(s);
     return hipGetLastError();
 }

@@ -943,6 +943,12 @@ __device__ __forceinline__ void stage_line_params(const StarDev& s, int l, int l
     }
 }
 
+}  // namespace pz
+
+#include "pz_split_gather.h"
+
+namespace pz {
+
 // ----------------------------------------------------------- reductions
 __device__ __forceinline__ void dev_scatter(const StarDev& s, int l) {
     if (l >= s.L) return;

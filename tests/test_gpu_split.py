@@ -67,3 +67,38 @@ def test_nonfinite_line_stays_in_its_window(gpu_lib):
     keep = np.arange(60) != 7
     wl.lines, wl.params = wl.lines.take(keep), W.Params(wl.params.dgf[keep], wl.params.ddamp[keep], wl.params.dA, 1.3)
     np.testing.assert_allclose(got[:, outside], O.line_opacity(wl)[:, outside], rtol=KAPPA_RTOL, atol=1e-30)
+
+
+@pytest.mark.parametrize("N,L,D,window,eta,fam", [
+    (33, 1, 2, 0.3, 0.0, False), (300, 15, 16, 0.3, 0.0, True), (517, 17, 25, 0.3, 0.0, False),
+    (400, 33, 49, 0.3, 1e-3, True), (400, 47, 80, 0.3, 0.0, True), (900, 65, 72, 0.3, 1e-3, False),
+    (3001, 40, 20, 4.0, 0.0, False),
+])
+def test_split_gradients_vs_oracle(gpu_lib, N, L, D, window, eta, fam):
+    """Line gradients at the ends of the 16-line, 16-pixel and 32-pixel steps of
+    the gather, plain, with the centre test and per damping family (the rule of
+    the other gradient tests: 1e-3 of a large entry, 1e-5 of the largest)."""
+    from test_gpu_adjoint import grad_close_cond
+    pz = gpu_lib
+    wl = _case(N, L, D, window)
+    wl.center_eta = eta
+    if fam:
+        rng = np.random.default_rng(3)
+        wl.params.ddamp_family = rng.normal(0.0, 0.2, (3, L))
+    s = np.random.default_rng(N).normal(size=N)
+    plan = pz.plan_for(wl, flags=pz.PZ_FLAG_DAMPING_FAMILIES if fam else 0)
+    e = lambda *n: torch.empty(n, device="cuda")  # noqa: E731
+    g = [e(L), e(3, L) if fam else e(L), e(4), e(1)]
+    seed = torch.as_tensor(s.astype(np.float32), device="cuda")
+    print("synth_backward N=%d L=%d D=%d" % (N, L, D), flush=True)
+    pz.synth_backward(plan, pz.Atmos(wl.atm), pz.Params.from_host(wl.params), seed, *g)
+    got = [t.cpu().numpy().astype(np.float64) for t in g]
+    ref = O.adjoint(wl, wl.params, s.astype(np.float32).astype(np.float64), conditions=True)
+    grad_close_cond(got[0], ref["g_loggf"], ref["abs_loggf"], name="loggf")
+    if fam:
+        for f in range(3):
+            grad_close_cond(got[1][f], ref["g_damp_family"][f], ref["abs_damp_family"][f], name="family %d" % f)
+    else:
+        grad_close_cond(got[1], ref["g_damp"], ref["abs_damp"], name="damp")
+    grad_close_cond(got[2], ref["g_abund"], ref["abs_abund"], name="abund")
+    grad_close_cond(got[3], ref["g_xi"], ref["abs_xi"], name="xi")
