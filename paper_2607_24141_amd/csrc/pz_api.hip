@@ -264,7 +264,7 @@ int pz_plan_create(const pz_grid* grid, const pz_lines* lines, int32_t n_species
     const size_t o_order = take((size_t)n_tiles * 4), o_qctr = take(4), o_wany = take(4);
     const size_t o_t32f = take((size_t)n_t32 * 4), o_t32l = take((size_t)n_t32 * 4), o_t32o = take((size_t)n_t32 * 4);
     const bool scatter_ws = (opts->flags & PZ_FLAG_SCATTERING) != 0;
-    const size_t o_sc = scatter_ws ? take((size_t)SC_WS_ARRAYS * D * Npad * 8) : 0;
+    const size_t o_sc = scatter_ws ? take((size_t)N * D * 8) : 0;
     const size_t o_sci = scatter_ws ? take((size_t)3 * Npad * 4) : 0;
     // Voigt evaluations per tile (orders the batched opacity work)
     auto tile_costs = [&](int px, int n) {

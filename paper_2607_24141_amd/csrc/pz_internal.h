@@ -65,7 +65,7 @@ struct StarDev {
     bool scatter;
     int sc_max_iter;
     double sc_tol;
-    double* sc;                  // scattering workspace, [SC_NARR][D][Npad] float64
+    double* sc;                  // converged source function of the total branch, [N][D]
     int* sc_iters;               // [3][Npad] iterations used (forward total, continuum, adjoint)
     // corrections (caller device memory; may be null except xi)
     const float* dgf;
@@ -115,7 +115,6 @@ struct StarDev {
 
 static constexpr int TILE = 32;          // pixels of a tile of the split sums
 static constexpr int RCHUNK = 2048;      // lines per reduction partial
-static constexpr int SC_WS_ARRAYS = 45;  // [D][Npad] float64 arrays of the scattering workspace
 static constexpr int MAX_CHUNK = 16;     // most lines per LDS chunk of the opacity tile
 
 // Kernel launchers (pz_kernels.hip).  Each enqueues on the stream and returns

@@ -124,12 +124,15 @@ __global__ __launch_bounds__(64) void k_flux_e2(StarDev s) {
     }
 }
 
-__global__ __launch_bounds__(192) void k_flux_scatter(StarDev s) {
-    dev_flux_scatter(s, blockIdx.x * 64 + threadIdx.x, blockIdx.y);
+// Sixteen lanes per pixel, 16 pixels per workgroup; blockIdx.y: the branch.
+template <int NP>
+__global__ __launch_bounds__(256) void k_flux_scatter(StarDev s) {
+    dev_flux_scatter<NP>(s, blockIdx.x * 16 + threadIdx.x / 16, blockIdx.y);
 }
 
-__global__ __launch_bounds__(192) void k_reverse_scatter(StarDev s) {
-    dev_reverse_scatter(s, blockIdx.x * 64 + threadIdx.x);
+template <int NP>
+__global__ __launch_bounds__(256) void k_reverse_scatter(StarDev s) {
+    dev_reverse_scatter<NP>(s, blockIdx.x * 16 + threadIdx.x / 16);
 }
 
 __global__ void k_debug_formal(int D, int n, const float* S, const float* tau, int quad, float* F) {
@@ -312,9 +315,31 @@ hipError_t launch_opacity(const StarDev& s, int chunk, hipStream_t st) {
     return s.center ? launch_opacity_tiles<true>(s, chunk, grid, st) : launch_opacity_tiles<false>(s, chunk, grid, st);
 }
 
+// NP depths per lane: the fewest that cover D on sixteen lanes (at least two,
+// so that lane 0 holds both depths of the surface extrapolation).
+template <int NP>
+static void launch_scatter_np(const StarDev& s, bool reverse, hipStream_t st) {
+    const unsigned n = (s.N + 15) / 16;
+    if (reverse)
+        k_reverse_scatter<NP><<<n, 256, 0, st>>>(s);
+    else
+        k_flux_scatter<NP><<<dim3(n, 2), 256, 0, st>>>(s);
+}
+
+static void launch_scatter(const StarDev& s, bool reverse, hipStream_t st) {
+    static_assert(MAXD <= 80, "five depths per lane");
+    switch ((s.D + 15) / 16) {
+        case 1:
+        case 2: launch_scatter_np<2>(s, reverse, st); break;
+        case 3: launch_scatter_np<3>(s, reverse, st); break;
+        case 4: launch_scatter_np<4>(s, reverse, st); break;
+        default: launch_scatter_np<5>(s, reverse, st); break;
+    }
+}
+
 hipError_t launch_flux(const StarDev& s, hipStream_t st) {
     if (s.scatter)
-        k_flux_scatter<<<dim3((s.N + 63) / 64, 2), dim3(64, 3), 0, st>>>(s);
+        launch_scatter(s, false, st);
     else if (s.quad == PZ_QUAD_E2)
         k_flux_e2<<<dim3((s.N + WAVE - 1) / WAVE, 2), WAVE, 0, st>>>(s);
     else
@@ -324,7 +349,7 @@ hipError_t launch_flux(const StarDev& s, hipStream_t st) {
 
 hipError_t launch_reverse_scan(const StarDev& s, hipStream_t st) {
     if (s.scatter)
-        k_reverse_scatter<<<(s.N + 63) / 64, dim3(64, 3), 0, st>>>(s);
+        launch_scatter(s, true, st);
     else if (s.quad == PZ_QUAD_E2)
         k_reverse_scan_e2<<<(s.N + 63) / 64, 64, 0, st>>>(s);
     else

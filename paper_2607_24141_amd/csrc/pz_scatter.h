@@ -11,13 +11,11 @@
 // Forward: the fixed point S* = eps B + (1 - eps) Lambda S* by accelerated
 // Lambda iteration (Jacobi with the diagonal Lambda*_jj of the same operator):
 //   S <- S + (eps B + (1 - eps) Lambda S - S) / (1 - (1 - eps) Lambda*),
-// from S = B until max_j |dS_j / S_j| <= tol (or the iteration cap), every
-// fourth iteration followed by Ng's extrapolation from the last four iterates
-// (Ng 1974: the combination of them whose next differences are smallest in
-// the relative least-squares sense), then the
-// emergent flux F = 2 pi sum_k w_k mu_k I+(0, mu_k).  Six threads per pixel:
-// the two branches, and in each the three ray directions, which sweep their
-// share of J in parallel and then update a third of the depths each.
+// from S = B until |dS_j| <= tol |S_j| at every depth (or the iteration cap),
+// every fourth iteration followed by Ng's extrapolation from the last four
+// iterates (Ng 1974: the combination of them whose next differences are
+// smallest in the relative least-squares sense), then the emergent flux
+// F = 2 pi sum_k w_k mu_k I+(0, mu_k).
 //
 // Backward (total branch): with gS = dF/dS* G and gtau the direct flux terms,
 // the adjoint lambda solves (I - diag(1 - eps) Lambda)^T lambda = gS by the same
@@ -26,537 +24,618 @@
 //   dL/dtau  += VJP of J(S*, tau) with the cotangent (1 - eps) lambda,
 //   dL/dchi   = trapezoid adjoint of dL/dtau,
 //   dL/dkappa_line_j = dL/dchi_j + dL/deps_j sigma_j / chi_j^2.
-// It runs on the same three threads per pixel (one per ray direction), reuses
-// the forward's segment tables, so no exponential is evaluated, and adds the
-// directions' partial sums in a fixed order.
-// Workspace columns are [D] with stride Npad (coalesced across pixels).
+//
+// Layout: sixteen lanes (a row of the wavefront) per pixel, lane q holding the
+// NP consecutive depths NP q .. NP q + NP - 1 and the segments that end at
+// them, all three directions, in registers.  A sweep along depth is a linear
+// recurrence I_j = e_j I_{j-1} + b_j: each lane runs its own NP steps, the rows
+// combine by a four-step scan (row shifts; the multipliers are products of e,
+// formed once per pixel), and each lane runs its steps again from its carry.
+// The iteration so touches no memory: with one thread per (pixel, direction)
+// and the segment coefficients in tables it moved 10.6 GB per launch at
+// 37,550 pixels (2.0 ms; the adjoint 4.6 GB, 1.3 ms), bound by HBM.  What is
+// left is float64 arithmetic, most of it the exponentials of the coefficients
+// (SCATTER_FIGURES).
+// Segment j runs from depth j - 1 to j (j = 0: from the surface); with S between
+// depths linear, e = e^-x, w = lw(x) and p = 1 - e^-x - lw(x):
+//   inward   I_j     = e_j I_{j-1} + p_j S_j + w_j S_{j-1},
+//   outward  I_{j-1} = e_j I_j + p_j S_{j-1} + w_j S_j.
 #pragma once
 
 namespace pz {
 
-struct Col {
-    double* p;
-    size_t st;
-    __device__ __forceinline__ double& operator[](int j) const { return p[(size_t)j * st]; }
-};
-
-// workspace arrays (each [D][Npad] float64): per branch b (tau, eps, S, Ld, B, the three
-// per-direction parts of J, the segment coefficients of each direction m: e^-x, 1 - e^-x, lw(x)
-// of the segment ending at depth j, j >= 1, and of the surface segment [0, tau_0] at j = 0, and
-// the three previous iterates of S), then
-// the backward's lambda, right-hand side and one intensity profile per direction.  The backward
-// keeps its per-direction partial sums in the continuum branch's columns, which it does not need.
-enum { SC_BR = 0, SC_TAU = 0, SC_EPS = 1, SC_S = 2, SC_LD = 3, SC_B = 4, SC_JM = 5, SC_CE = 8, SC_CO = 11,
-       SC_CL = 14, SC_H = 17, SC_PER_BR = 20, SC_LAM = 40, SC_RHS = 41, SC_IS = 42, SC_NARR = 45 };
-static_assert(SC_NARR == SC_WS_ARRAYS, "scattering workspace size");
-
-__device__ __forceinline__ Col sc_col(const StarDev& s, int id, int i) {
-    return Col{s.sc + (size_t)id * s.D * s.Npad + i, (size_t)s.Npad};
-}
-__device__ __forceinline__ Col sc_bcol(const StarDev& s, int b, int k, int i) {
-    return sc_col(s, SC_BR + SC_PER_BR * b + k, i);
-}
 __device__ __forceinline__ double sc_mu(int k) { return k == 0 ? kMu0 : (k == 1 ? kMu1 : kMu2); }
 __device__ __forceinline__ double sc_hw(int k) { return k == 1 ? 0.5 * 8.0 / 18.0 : 0.5 * 5.0 / 18.0; }   // w_k / 2
 
-// d(S_top)/d(tau_0), d(S_top)/d(tau_1) with S_top = S_0 - tau_0 (S_1 - S_0) / (tau_1 - tau_0)
-__device__ __forceinline__ void sc_top_dtau(const Col& tau, const Col& S, double& d0, double& d1) {
-    const double t0 = tau[0], dt = tau[1] - t0, sig = (S[1] - S[0]) / dt;
-    d0 = -sig - t0 * sig / dt;
-    d1 = t0 * sig / dt;
+// Row shifts of a float64 (zero enters): shr<n> takes the value n lanes below,
+// shl<n> n lanes above, within the row of 16.
+template <int CTRL>
+__device__ __forceinline__ double row_move(double x) {
+    const unsigned long long u = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+template <int n>
+__device__ __forceinline__ double shr(double x) { return row_move<0x110 + n>(x); }
+template <int n>
+__device__ __forceinline__ double shl(double x) { return row_move<0x100 + n>(x); }
+
+// Sum and maximum over the row, the same value in every lane (a fixed order).
+__device__ __forceinline__ double row_sum(double x) {
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) x += __shfl_xor(x, o, WAVE);
+    return x;
+}
+__device__ __forceinline__ double row_max(double x) {
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) x = fmax(x, __shfl_xor(x, o, WAVE));
+    return x;
+}
+// Whether every lane of this lane's row holds c.
+__device__ __forceinline__ bool row_all(bool c) {
+    const unsigned long long b = __builtin_amdgcn_ballot_w64(!c);
+    return ((b >> (threadIdx.x & 48)) & 0xffffull) == 0;
 }
 
+// One branch of one pixel, spread over its row.
+template <int NP>
 struct ScPixel {
-    double kc, c1, c2, fs;   // continuum, Planck constants, sigma scale (lambda/lambda_ref)^sigma_alpha
+    int D, q;                        // depths; lane of the row
+    bool last;                       // holds depth D - 1
+    int kd;                          // ... as its k = kd (uniform)
+    double e[3][NP], p[3][NP], w[3][NP];   // segments; none past D - 1 (e = 1); lane 0: e_0 = 0, w_0 = 0, p_0 the weight of S_0 in I-_0
+    double cw[3];                    // lane 0: -(the weight of S_1 in I-_0); else 0
+    double P[3][4], Q[3][4];         // scan multipliers of the sweeps down and up
+    double dt[NP];                   // tau_j - tau_{j-1} (j = 0: tau_0)
+    double gd;                       // 1 / (tau_{D-1} - tau_{D-2}), in the last lane
+    double eps[NP], inv[NP];         // eps and 1 / (1 - (1 - eps) Lambda*)
+    double chi[NP];
+    double kc, c1, c2, fs;
+
+    __device__ __forceinline__ int depth(int k) const { return q * NP + k; }
+
+    // S_{D-1} and S_{D-2} in the last lane (prev: the depth above the lane's first)
+    __device__ __forceinline__ void bottom(const double* S, double prev, double& sd, double& sd2) const {
+        sd = S[0];
+        sd2 = prev;
+#pragma unroll
+        for (int k = 1; k < NP; ++k)
+            if (k == kd) {
+                sd = S[k];
+                sd2 = S[k - 1];
+            }
+    }
+
+    __device__ __forceinline__ double scan_down(int m, double r) const {
+        r = fma(P[m][0], shr<1>(r), r);
+        r = fma(P[m][1], shr<2>(r), r);
+        r = fma(P[m][2], shr<4>(r), r);
+        return fma(P[m][3], shr<8>(r), r);
+    }
+    __device__ __forceinline__ double scan_up(int m, double r) const {
+        r = fma(Q[m][0], shl<1>(r), r);
+        r = fma(Q[m][1], shl<2>(r), r);
+        r = fma(Q[m][2], shl<4>(r), r);
+        return fma(Q[m][3], shl<8>(r), r);
+    }
+
+    // I- of S along direction m at the lane's depths; prev = S above its first depth.
+    __device__ __forceinline__ void inward(int m, const double* S, double prev, double* I) const {
+        double b[NP], a = 0.0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            b[k] = fma(S[k], p[m][k], (k ? S[k - 1] : prev) * w[m][k]);
+            if (k == 0) b[0] = fma(-cw[m], S[1], b[0]);
+            a = fma(e[m][k], a, b[k]);
+        }
+        double c = shr<1>(scan_down(m, a));
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            c = fma(e[m][k], c, b[k]);
+            I[k] = c;
+        }
+    }
+
+    // I+ of S along direction m at the lane's depths.
+    __device__ __forceinline__ void outward(int m, const double* S, double prev, double* I) const {
+        double sd, sd2;
+        bottom(S, prev, sd, sd2);
+        const double bnd = last ? fma(sc_mu(m) * gd, sd - sd2, sd) : 0.0;
+        double b[NP], a = bnd;
+#pragma unroll
+        for (int k = NP - 1; k >= 0; --k) {
+            b[k] = fma(k ? S[k - 1] : prev, p[m][k], S[k] * w[m][k]);
+            a = fma(e[m][k], a, b[k]);
+        }
+        double c = shl<1>(scan_up(m, a));
+        if (last) c = bnd;
+#pragma unroll
+        for (int k = NP - 1; k >= 0; --k) {
+            I[k] = c;
+            c = fma(e[m][k], c, b[k]);
+        }
+    }
+
+    // J = Lambda S
+    __device__ __forceinline__ void lambda(const double* S, double* J) const {
+        const double prev = shr<1>(S[NP - 1]);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) J[k] = 0.0;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            double I[NP];
+            inward(m, S, prev, I);
+#pragma unroll
+            for (int k = 0; k < NP; ++k) J[k] = fma(sc_hw(m), I[k], J[k]);
+            outward(m, S, prev, I);
+#pragma unroll
+            for (int k = 0; k < NP; ++k) J[k] = fma(sc_hw(m), I[k], J[k]);
+        }
+    }
+
+    // G_j = e_j G_{j-1} + v_j (down), at the lane's depths; in: G above its first depth
+    __device__ __forceinline__ void adjoint_down(int m, const double* v, double* G, double& in) const {
+        double a = 0.0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) a = fma(e[m][k], a, v[k]);
+        double c = in = shr<1>(scan_down(m, a));
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            c = fma(e[m][k], c, v[k]);
+            G[k] = c;
+        }
+    }
+    // G_j = e_{j+1} G_{j+1} + v_j (up)
+    __device__ __forceinline__ void adjoint_up(int m, const double* v, double* G) const {
+        double a = 0.0;
+#pragma unroll
+        for (int k = NP - 1; k >= 0; --k) a = e[m][k] * (a + v[k]);
+        double c = shl<1>(scan_up(m, a));
+        if (last) c = 0.0;
+#pragma unroll
+        for (int k = NP - 1; k >= 0; --k) {
+            G[k] = c + v[k];
+            c = e[m][k] * G[k];
+        }
+    }
+
+    // out += the transpose of S -> I+ along m for the down-swept G (gin above the lane): adds
+    // G_{j-1} (p_j at j - 1, w_j at j) and the bottom boundary; what falls on the depth above the
+    // lane's first goes to back.
+    __device__ __forceinline__ void outward_T(int m, const double* G, double gin, double* out, double& back) const {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const double g = k ? G[k - 1] : gin;
+            out[k] = fma(g, w[m][k], out[k]);
+            if (k)
+                out[k - 1] = fma(g, p[m][k], out[k - 1]);
+            else
+                back = fma(g, p[m][0], back);
+        }
+        if (last) {
+            const double f = sc_mu(m) * gd;
+#pragma unroll
+            for (int k = 0; k < NP; ++k)
+                if (k == kd) {
+                    out[k] = fma(G[k], 1.0 + f, out[k]);
+                    if (k)
+                        out[k - 1] = fma(-G[k], f, out[k - 1]);
+                    else
+                        back = fma(-G[k], f, back);
+                }
+        }
+    }
+    // out += the transpose of S -> I- along m for the up-swept G
+    __device__ __forceinline__ void inward_T(int m, const double* G, double* out, double& back) const {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            out[k] = fma(G[k], p[m][k], out[k]);
+            if (k)
+                out[k - 1] = fma(G[k], w[m][k], out[k - 1]);
+            else
+                back = fma(G[0], w[m][0], back);
+        }
+        out[1] = fma(-cw[m], G[0], out[1]);
+    }
+
+    // Lambda^T v
+    __device__ __forceinline__ void lambda_T(const double* v, double* out) const {
+        double back = 0.0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) out[k] = 0.0;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            double h[NP], G[NP], in;
+#pragma unroll
+            for (int k = 0; k < NP; ++k) h[k] = sc_hw(m) * v[k];
+            adjoint_down(m, h, G, in);
+            outward_T(m, G, in, out, back);
+            adjoint_up(m, h, G);
+            inward_T(m, G, out, back);
+        }
+        out[NP - 1] += shl<1>(back);
+    }
+
+    // chi, eps, the segments and Lambda* of branch b at pixel i; B: Planck function at the lane's depths.
+    __device__ __forceinline__ void setup(const StarDev& s, int i, int b, double* B) {
+        D = s.D;
+        q = threadIdx.x & 15;
+        kd = (D - 1) % NP;
+        last = q == (D - 1) / NP;
+        const double lnl = log(s.lam_first_nm) + (double)i * s.h;
+        const double lam_cm = exp(lnl) * 1.0e-7;
+        kc = s.kappa0 * exp(s.alpha * (lnl - log(s.lam_ref_nm)));
+        const double l2 = lam_cm * lam_cm;
+        c1 = 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7;
+        c2 = H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ);
+        fs = exp(s.sigma_alpha * (lnl - log(s.lam_ref_nm)));
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int j = min(depth(k), D - 1);
+            const double ka = kc + (b == 0 ? (double)s.kappa[(size_t)j * s.Npad + i] : 0.0);
+            chi[k] = ka + s.sigma_c[j] * fs;
+            eps[k] = ka / chi[k];
+            B[k] = c1 / expm1(c2 / s.T[j]);
+        }
+        const double above = shr<1>(chi[NP - 1]);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int j = depth(k);
+            const double mj = s.m[min(j, D - 1)];
+            dt[k] = j == 0 ? chi[0] * mj : 0.5 * ((k ? chi[k - 1] : above) + chi[k]) * (mj - s.m[max(min(j, D - 1) - 1, 0)]);
+        }
+        {
+            double d = dt[0];
+#pragma unroll
+            for (int k = 1; k < NP; ++k)
+                if (k == kd) d = dt[k];
+            gd = last ? 1.0 / d : 0.0;
+        }
+        const double c = q == 0 ? dt[0] / dt[1] : 0.0;    // tau_0 / (tau_1 - tau_0)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const double imu = 1.0 / sc_mu(m);
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const ExpTerms64 t = exp_terms64(dt[k] * imu);
+                const bool in = depth(k) < D;
+                e[m][k] = in ? t.e : 1.0;
+                p[m][k] = in ? t.om - t.lw : 0.0;
+                w[m][k] = in ? t.lw : 0.0;
+            }
+            cw[m] = 0.0;
+            if (q == 0) {                                 // the surface segment: S_top by extrapolation
+                cw[m] = c * w[m][0];
+                p[m][0] = p[m][0] + w[m][0] + cw[m];
+                w[m][0] = 0.0;
+                e[m][0] = 0.0;
+            }
+        }
+        double L[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) L[k] = 0.0;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const double below = shl<1>(p[m][0]);         // the next lane's first segment
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                double out = k + 1 < NP ? p[m][k + 1] : below, in = p[m][k];
+                if (last && k == kd) out = fma(sc_mu(m), gd, 1.0);
+                // depth D - 2 and depth 1 share a boundary's extrapolation
+                if (k == 1) in = fma(-e[m][1], cw[m], in);
+                L[k] = fma(sc_hw(m), out + in, L[k]);
+            }
+            // Lambda*_{D-2} loses e_{D-1} mu / dtau of the diffusion boundary
+            double x = 0.0;
+            if (last)
+#pragma unroll
+                for (int k = 0; k < NP; ++k)
+                    if (k == kd) {
+                        const double f = sc_hw(m) * e[m][k] * sc_mu(m) * gd;
+                        if (k)
+                            L[k - 1] -= f;
+                        else
+                            x = f;
+                    }
+            L[NP - 1] -= shl<1>(x);
+            double E = 1.0;
+#pragma unroll
+            for (int k = 0; k < NP; ++k) E *= e[m][k];
+            double f = E, g = last ? 0.0 : E;
+            P[m][0] = f;
+            f *= shr<1>(f);
+            P[m][1] = f;
+            f *= shr<2>(f);
+            P[m][2] = f;
+            f *= shr<4>(f);
+            P[m][3] = f;
+            Q[m][0] = g;
+            g *= shl<1>(g);
+            Q[m][1] = g;
+            g *= shl<2>(g);
+            Q[m][2] = g;
+            g *= shl<4>(g);
+            Q[m][3] = g;
+        }
+#pragma unroll
+        for (int k = 0; k < NP; ++k) inv[k] = 1.0 / (1.0 - (1.0 - eps[k]) * L[k]);
+    }
 };
 
-__device__ __forceinline__ ScPixel sc_pixel(const StarDev& s, int i) {
-    const double lnl = log(s.lam_first_nm) + (double)i * s.h;
-    const double lam_cm = exp(lnl) * 1.0e-7;
-    ScPixel p;
-    p.kc = s.kappa0 * exp(s.alpha * (lnl - log(s.lam_ref_nm)));
-    const double l2 = lam_cm * lam_cm;
-    p.c1 = 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7;
-    p.c2 = H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ);
-    p.fs = exp(s.sigma_alpha * (lnl - log(s.lam_ref_nm)));
-    return p;
-}
+// S* of the total branch, kept for the backward: [N][D].
+__device__ __forceinline__ double* sc_source(const StarDev& s, int i) { return s.sc + (size_t)i * s.D; }
 
-// tau, eps and B of branch b; S starts at B
-__device__ inline void sc_setup(const StarDev& s, int i, int b, const ScPixel& p) {
-    const int D = s.D;
-    const Col B = sc_bcol(s, b, SC_B, i), tau = sc_bcol(s, b, SC_TAU, i), eps = sc_bcol(s, b, SC_EPS, i),
-              S = sc_bcol(s, b, SC_S, i);
-    const float* kl = s.kappa + i;
-    double chi_prev = 0.0, t = 0.0;
-    for (int j = 0; j < D; ++j) {
-        const double ka = p.kc + (b == 0 ? (double)kl[(size_t)j * s.Npad] : 0.0);
-        const double chi = ka + s.sigma_c[j] * p.fs;
-        t = (j == 0) ? chi * s.m[0] : t + 0.5 * (chi_prev + chi) * (s.m[j] - s.m[j - 1]);
-        chi_prev = chi;
-        tau[j] = t;
-        eps[j] = ka / chi;
-        const double Bj = p.c1 / expm1(p.c2 / s.T[j]);
-        B[j] = Bj;
-        S[j] = Bj;
-    }
-}
-
-// Segment coefficients of direction m (see the workspace layout)
-__device__ inline void sc_coeffs(int D, const Col& tau, int m, const Col& CE, const Col& CO, const Col& CL) {
-    const double mu = sc_mu(m);
-    double ta = 0.0;
-    for (int j = 0; j < D; ++j) {
-        const double tb = tau[j];
-        const ExpTerms64 et = exp_terms64((tb - ta) / mu);
-        CE[j] = et.e;
-        CO[j] = et.om;
-        CL[j] = et.lw;
-        ta = tb;
-    }
-}
-
-// Lambda*_jj for the depths j = m, m + 3, ... (the coefficient of S_j in J_j),
-// from the coefficients of all three directions
-__device__ inline void sc_lambda_diag_part(int D, const Col& tau, const Col& Ld, int m, const Col* CE, const Col* CO,
-                                           const Col* CL) {
-    const double t0 = tau[0], c = t0 / (tau[1] - t0), gD = 1.0 / (tau[D - 1] - tau[D - 2]);
-    for (int j = m; j < D; j += 3) {
-        double acc = 0.0;
+// Ng's extrapolation of S from x0 = S and the previous iterates x1, x2, x3:
+// with d0 = x0 - x1, d1 = x1 - x2, d2 = x2 - x3 and weights 1/x0^2, (a, c)
+// minimise |d0 - a (d0 - d1) - c (d0 - d2)|^2 and S <- (1 - a - c) x0 + a x1 +
+// c x2; the one-term form (c = 0) when d0 - d1 and d0 - d2 are nearly parallel.
+template <int NP>
+__device__ __forceinline__ void sc_ng(const ScPixel<NP>& x, double* S, const double* x1, const double* x2,
+                                      const double* x3, bool active) {
+    double r[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double mu = sc_mu(k);
-            double out, in;
-            if (j == D - 1) {
-                out = 1.0 + mu * gD;
-            } else {
-                out = CO[k][j + 1] - CL[k][j + 1];
-                if (j == D - 2) out -= CE[k][j + 1] * mu * gD;
-            }
-            if (j == 0) {
-                in = CO[k][0] + c * CL[k][0];
-            } else {
-                in = CO[k][j] - CL[k][j];
-                if (j == 1) in -= CE[k][1] * c * CL[k][0];
-            }
-            acc += sc_hw(k) * (out + in);
+    for (int k = 0; k < NP; ++k)
+        if (x.depth(k) < x.D) {
+            const double d0 = S[k] - x1[k], u = d0 - (x1[k] - x2[k]), v = d0 - (x2[k] - x3[k]);
+            const double wt = 1.0 / (S[k] * S[k]);
+            r[0] += wt * u * u;
+            r[1] += wt * u * v;
+            r[2] += wt * v * v;
+            r[3] += wt * d0 * u;
+            r[4] += wt * d0 * v;
         }
-        Ld[j] = acc;
-    }
-}
-
-// Jm = w_m/2 (I+ + I-) along direction m (one third of J = Lambda S)
-__device__ inline void sc_lambda_mu(int D, const Col& tau, const Col& S, const Col& Jm, int m, const Col& CE,
-                                    const Col& CO, const Col& CL) {
-    const double mu = sc_mu(m), hw = sc_hw(m);
-    double I;
-    {
-        const double t0 = tau[0], S0 = S[0];
-        const double S_top = S0 - t0 * (S[1] - S0) / (tau[1] - t0);
-        I = S0 * CO[0] + (S_top - S0) * CL[0];
-        Jm[0] = hw * I;
-    }
-    double Sa = S[0];
-    for (int j = 1; j < D; ++j) {
-        const double Sb = S[j];
-        I = I * CE[j] + Sb * CO[j] + (Sa - Sb) * CL[j];
-        Jm[j] = hw * I;
-        Sa = Sb;
-    }
-    const double SD = S[D - 1];
-    I = SD + mu * (SD - S[D - 2]) / (tau[D - 1] - tau[D - 2]);
-    Jm[D - 1] += hw * I;
-    double Sb = SD;
-    for (int j = D - 2; j >= 0; --j) {
-        const double Sj = S[j];
-        I = I * CE[j + 1] + Sj * CO[j + 1] + (Sb - Sj) * CL[j + 1];
-        Jm[j] += hw * I;
-        Sb = Sj;
-    }
-}
-
-// 2 pi w_m mu_m I+(0, mu_m) of S
-__device__ inline double sc_flux_mu(int D, const Col& tau, const Col& S, int m, const Col& CE, const Col& CO,
-                                    const Col& CL) {
-    const double mu = sc_mu(m);
-    const double SD = S[D - 1];
-    double I = SD + mu * (SD - S[D - 2]) / (tau[D - 1] - tau[D - 2]);
-    double Sb = SD;
-    for (int j = D - 2; j >= 0; --j) {
-        const double Sj = S[j];
-        I = I * CE[j + 1] + Sj * CO[j + 1] + (Sb - Sj) * CL[j + 1];
-        Sb = Sj;
-    }
-    const double t0 = tau[0], S0 = S[0];
-    const double S_top = S0 - t0 * (S[1] - S0) / (tau[1] - t0);
-    return 2.0 * PI * 2.0 * sc_hw(m) * mu * (I * CE[0] + S_top * CO[0] + (S0 - S_top) * CL[0]);
-}
-
-// Ng's extrapolation of one pixel's S from x0 = S (iterate it) and the
-// previous iterates x1, x2, x3 in H[(it - k) % 3]: with d0 = x0 - x1,
-// d1 = x1 - x2, d2 = x2 - x3 and weights 1/x0^2, (a, b) minimise
-// |d0 - a (d0 - d1) - b (d0 - d2)|^2 and S <- (1 - a - b) x0 + a x1 + b x2;
-// the one-term form (b = 0) when d0 - d1 and d0 - d2 are nearly parallel.
-// Called by every thread of the workgroup (it synchronises it); ng: the
-// pixel is still iterating.  The depth sums are split over the three
-// direction threads and added in a fixed order.
-__device__ inline void sc_ng_step(int D, const Col& S, const Col* H, int it, bool ng, int m, int tx,
-                                  double (*ngs)[3][64]) {
-    const Col &h1 = H[(it - 1) % 3], &h2 = H[(it - 2) % 3], &h3 = H[(it - 3) % 3];
-    double p[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (ng) {
-        for (int j = m; j < D; j += 3) {
-            const double x0 = S[j], x1 = h1[j], x2 = h2[j], x3 = h3[j];
-            const double d0 = x0 - x1, u = d0 - (x1 - x2), v = d0 - (x2 - x3), w = 1.0 / (x0 * x0);
-            p[0] += w * u * u;
-            p[1] += w * u * v;
-            p[2] += w * v * v;
-            p[3] += w * d0 * u;
-            p[4] += w * d0 * v;
-        }
-    }
 #pragma unroll
-    for (int k = 0; k < 5; ++k) ngs[k][m][tx] = p[k];
-    __syncthreads();
-    if (m == 0 && ng) {
-        double q[5];
+    for (int k = 0; k < 5; ++k) r[k] = row_sum(r[k]);
+    const double det = r[0] * r[2] - r[1] * r[1];
+    double a = 0.0, c = 0.0;
+    if (det > 1e-10 * r[0] * r[2]) {
+        a = (r[3] * r[2] - r[4] * r[1]) / det;
+        c = (r[4] * r[0] - r[3] * r[1]) / det;
+    } else if (r[0] > 0.0) {
+        a = r[3] / r[0];
+    }
+    if (!(isfinite(a) && isfinite(c))) a = c = 0.0;
+    if (active)
 #pragma unroll
-        for (int k = 0; k < 5; ++k) q[k] = ngs[k][0][tx] + ngs[k][1][tx] + ngs[k][2][tx];
-        const double det = q[0] * q[2] - q[1] * q[1];
-        double a = 0.0, c = 0.0;
-        if (det > 1e-10 * q[0] * q[2]) {
-            a = (q[3] * q[2] - q[4] * q[1]) / det;
-            c = (q[4] * q[0] - q[3] * q[1]) / det;
-        } else if (q[0] > 0.0) {
-            a = q[3] / q[0];
-        }
-        if (!(isfinite(a) && isfinite(c))) a = c = 0.0;
-        ngs[0][0][tx] = a;
-        ngs[1][0][tx] = c;
-    }
-    __syncthreads();
-    if (ng) {
-        const double a = ngs[0][0][tx], c = ngs[1][0][tx];
-        for (int j = m; j < D; j += 3) S[j] = (1.0 - a - c) * S[j] + a * h1[j] + c * h2[j];
-    }
-    __syncthreads();
+        for (int k = 0; k < NP; ++k) S[k] = (1.0 - a - c) * S[k] + a * x1[k] + c * x2[k];
 }
 
-// Forward of one branch for 64 pixels: a workgroup of 64 x 3 threads,
-// threadIdx.y = m the ray direction (called by every thread: it synchronises
-// the workgroup).  Each iteration every direction sweeps into its part of J;
-// then each thread updates the depths j = m (mod 3) of its pixel.  A pixel
-// stops at max_j |dS_j / S_j| <= tol or the cap and its S is then frozen, so
-// its result does not depend on the other pixels of the workgroup.
-__device__ inline void dev_flux_scatter(const StarDev& s, int i, int b) {
-    __shared__ double red[3][64];
-    __shared__ double ngs[5][3][64];
-    __shared__ int done[64];
-    const int tx = threadIdx.x, m = threadIdx.y, D = s.D;
+// Forward of branch b at pixel i, one row of lanes (all 64 lanes of a
+// wavefront call this; i beyond the grid computes the last pixel and stores
+// nothing).  A pixel's S is frozen when it has converged, so its result does
+// not depend on the wavefront's other pixels.
+template <int NP>
+__device__ __forceinline__ void dev_flux_scatter(const StarDev& s, int i, int b) {
     const bool px = i < s.N;
-    const Col tau = sc_bcol(s, b, SC_TAU, i), eps = sc_bcol(s, b, SC_EPS, i), S = sc_bcol(s, b, SC_S, i),
-              Ld = sc_bcol(s, b, SC_LD, i), B = sc_bcol(s, b, SC_B, i);
-    const Col Jm[3] = {sc_bcol(s, b, SC_JM, i), sc_bcol(s, b, SC_JM + 1, i), sc_bcol(s, b, SC_JM + 2, i)};
-    const Col CE[3] = {sc_bcol(s, b, SC_CE, i), sc_bcol(s, b, SC_CE + 1, i), sc_bcol(s, b, SC_CE + 2, i)};
-    const Col CO[3] = {sc_bcol(s, b, SC_CO, i), sc_bcol(s, b, SC_CO + 1, i), sc_bcol(s, b, SC_CO + 2, i)};
-    const Col CL[3] = {sc_bcol(s, b, SC_CL, i), sc_bcol(s, b, SC_CL + 1, i), sc_bcol(s, b, SC_CL + 2, i)};
-    const Col H[3] = {sc_bcol(s, b, SC_H, i), sc_bcol(s, b, SC_H + 1, i), sc_bcol(s, b, SC_H + 2, i)};
-    if (px && m == 0) sc_setup(s, i, b, sc_pixel(s, i));
-    if (m == 0) done[tx] = px ? 0 : 1;
-    __syncthreads();
-    if (px) sc_coeffs(D, tau, m, CE[m], CO[m], CL[m]);
-    __syncthreads();
-    if (px) sc_lambda_diag_part(D, tau, Ld, m, CE, CO, CL);
-    int it = 0;
-    for (;;) {
-        const bool active = px && !done[tx];
-        if (active) sc_lambda_mu(D, tau, S, Jm[m], m, CE[m], CO[m], CL[m]);
-        __syncthreads();
-        double dmax = 0.0;
-        if (active) {
-            const Col& Hs = H[it % 3];                // iterate `it` becomes history
-            for (int j = m; j < D; j += 3) {
-                const double e = eps[j], Sj = S[j];
-                const double J = Jm[0][j] + Jm[1][j] + Jm[2][j];
-                const double Sn = Sj + (e * B[j] + (1.0 - e) * J - Sj) / (1.0 - (1.0 - e) * Ld[j]);
-                dmax = fmax(dmax, fabs(Sn - Sj) / fabs(Sn));
-                Hs[j] = Sj;
-                S[j] = Sn;
-            }
-        }
-        red[m][tx] = dmax;
-        ++it;
-        __syncthreads();
-        if (m == 0 && active) {
-            const double d = fmax(red[0][tx], fmax(red[1][tx], red[2][tx]));
-            if (d <= s.sc_tol || it >= s.sc_max_iter) {
-                done[tx] = 1;
-                if (s.sc_iters) s.sc_iters[b * s.Npad + i] = it;
-            }
-        }
-        __syncthreads();
-        if (it % 4 == 0) sc_ng_step(D, S, H, it, px && !done[tx], m, tx, ngs);
-        if (!__syncthreads_or(!done[tx])) break;
+    i = min(i, s.N - 1);
+    ScPixel<NP> x;
+    double B[NP], S[NP], x1[NP], x2[NP], x3[NP];
+    x.setup(s, i, b, B);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        S[k] = x1[k] = x2[k] = x3[k] = B[k];
+        B[k] *= x.eps[k];
     }
-    const double f = px ? sc_flux_mu(D, tau, S, m, CE[m], CO[m], CL[m]) : 0.0;
-    red[m][tx] = f;
-    __syncthreads();
-    if (px && m == 0) {
+    bool active = true;
+    int iters = 0;
+    for (int it = 1;; ++it) {
+        double J[NP];
+        x.lambda(S, J);
+        bool ok = true;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const double Sn = S[k] + (B[k] + (1.0 - x.eps[k]) * J[k] - S[k]) * x.inv[k];
+            if (x.depth(k) < x.D && fabs(Sn - S[k]) > s.sc_tol * fabs(Sn)) ok = false;
+            x3[k] = x2[k];
+            x2[k] = x1[k];
+            x1[k] = S[k];
+            S[k] = active ? Sn : S[k];
+        }
+        if (active && (row_all(ok) || it >= s.sc_max_iter)) {
+            active = false;
+            iters = it;
+        }
+        if (!wave_any(active)) break;
+        if (it % 4 == 0) sc_ng<NP>(x, S, x1, x2, x3, active);
+    }
+    const double prev = shr<1>(S[NP - 1]);
+    double f = 0.0;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        double I[NP];
+        x.outward(m, S, prev, I);
+        if (x.q == 0) {                                   // through the surface segment
+            const ExpTerms64 t = exp_terms64(x.dt[0] / sc_mu(m));
+            const double S_top = S[0] - x.dt[0] * (S[1] - S[0]) / x.dt[1];
+            f += 2.0 * PI * 2.0 * sc_hw(m) * sc_mu(m) * (I[0] * t.e + S_top * t.om + (S[0] - S_top) * t.lw);
+        }
+    }
+    if (!px) return;
+    if (x.q == 0) {
         float* out = b == 0 ? s.F : s.Fc;
-        if (out) out[i] = (float)(red[0][tx] + red[1][tx] + red[2][tx]);
+        if (out) out[i] = (float)f;
+        if (s.sc_iters) s.sc_iters[b * s.Npad + i] = iters;
     }
+    if (b == 0)
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            if (x.depth(k) < x.D) sc_source(s, i)[x.depth(k)] = S[k];
 }
 
-// lw'(x) = e^-x - lw(x) / x of a segment of length x with coefficients e^-x and lw(x)
-__device__ __forceinline__ double sc_dlw(double e, double lw, double x) { return e - lw / x; }
-
-// I+_j along direction m into IS (bottom-up), from the segment tables
-__device__ inline void sc_out_mu(int D, const Col& tau, const Col& S, int m, const Col& CE, const Col& CO,
-                                 const Col& CL, const Col& IS) {
-    const double SD = S[D - 1];
-    double I = SD + sc_mu(m) * (SD - S[D - 2]) / (tau[D - 1] - tau[D - 2]);
-    IS[D - 1] = I;
-    double Sb = SD;
-    for (int j = D - 2; j >= 0; --j) {
-        const double Sj = S[j];
-        I = I * CE[j + 1] + Sj * CO[j + 1] + (Sb - Sj) * CL[j + 1];
-        IS[j] = I;
-        Sb = Sj;
-    }
-}
-
-// I-_j along direction m into IS (top-down)
-__device__ inline void sc_in_mu(int D, const Col& tau, const Col& S, const Col& CE, const Col& CO, const Col& CL,
-                                const Col& IS) {
-    const double t0 = tau[0], S0 = S[0];
-    const double S_top = S0 - t0 * (S[1] - S0) / (tau[1] - t0);
-    double I = S0 * CO[0] + (S_top - S0) * CL[0];
-    IS[0] = I;
-    double Sa = S0;
-    for (int j = 1; j < D; ++j) {
-        const double Sb = S[j];
-        I = I * CE[j] + Sb * CO[j] + (Sa - Sb) * CL[j];
-        IS[j] = I;
-        Sa = Sb;
-    }
-}
-
-// Direction m's part of the flux VJP for the seed G = dL/dF: its dF/dS G into gS and its tau
-// terms into gt (both overwritten); leaves I+ of S in IS.
-__device__ inline void sc_flux_vjp_mu(int D, const Col& tau, const Col& S, double G, int m, const Col& CE,
-                                      const Col& CO, const Col& CL, const Col& IS, const Col& gS, const Col& gt) {
-    sc_out_mu(D, tau, S, m, CE, CO, CL, IS);
-    for (int j = 2; j < D; ++j) {
-        gS[j] = 0.0;
-        gt[j] = 0.0;
-    }
-    const double mu = sc_mu(m);
-    const double t0 = tau[0], S0 = S[0], dt01 = tau[1] - t0;
-    const double S_top = S0 - t0 * (S[1] - S0) / dt01;
-    double d0, d1;
-    sc_top_dtau(tau, S, d0, d1);
-    const double g0 = G * 2.0 * PI * 2.0 * sc_hw(m) * mu;           // dL/dI(0, mu_m)
-    {
-        const double e = CE[0], lw = CL[0], dlw = sc_dlw(e, lw, t0 / mu);
-        const double gStop = g0 * (CO[0] - lw);
-        gt[0] = g0 * (-IS[0] * e + S_top * e + (S0 - S_top) * dlw) / mu + gStop * d0;
-        gt[1] = gStop * d1;
-        gS[0] = g0 * lw + gStop * (1.0 + t0 / dt01);
-        gS[1] = gStop * (-t0 / dt01);
-    }
-    double Gk = g0 * CE[0];                                           // dL/dI+(tau_0)
-    for (int j = 0; j < D - 1; ++j) {
-        const double Sj = S[j], Sn = S[j + 1];
-        const double e = CE[j + 1], lw = CL[j + 1], dlw = sc_dlw(e, lw, (tau[j + 1] - tau[j]) / mu);
-        const double gx = Gk * (-IS[j + 1] * e + Sj * e + (Sn - Sj) * dlw) / mu;
-        gS[j] += Gk * (CO[j + 1] - lw);
-        gS[j + 1] += Gk * lw;
-        gt[j + 1] += gx;
-        gt[j] -= gx;
-        Gk *= e;
-    }
-    {
-        const double dS = S[D - 1] - S[D - 2], dt = tau[D - 1] - tau[D - 2];
-        gS[D - 1] += Gk * (1.0 + mu / dt);
-        gS[D - 2] -= Gk * mu / dt;
-        const double gd = Gk * (-mu * dS / (dt * dt));
-        gt[D - 1] += gd;
-        gt[D - 2] -= gd;
-    }
-}
-
-// out = direction m's part of Lambda^T v (overwritten).  Each sweep carries the pending term of
-// the next depth, so the first sweep writes every element once and the second adds once.
-__device__ inline void sc_lambda_T_mu(int D, const Col& tau, const Col& v, const Col& out, int m, const Col& CE,
-                                      const Col& CO, const Col& CL) {
-    const double mu = sc_mu(m), hw = sc_hw(m);
-    // transpose of the outward sweep, surface first
-    double G = 0.0, carry = 0.0;
-    for (int j = 0; j < D - 1; ++j) {
-        G += hw * v[j];
-        const double lw = CL[j + 1];
-        out[j] = carry + G * (CO[j + 1] - lw);
-        carry = G * lw;
-        G *= CE[j + 1];
-    }
-    {
-        const double g = mu / (tau[D - 1] - tau[D - 2]);
-        G += hw * v[D - 1];
-        out[D - 1] = carry + G * (1.0 + g);
-        out[D - 2] -= G * g;
-    }
-    // transpose of the inward sweep, deepest first
-    G = 0.0;
-    carry = 0.0;
-    for (int j = D - 1; j >= 1; --j) {
-        G += hw * v[j];
-        const double lw = CL[j];
-        out[j] += carry + G * (CO[j] - lw);
-        carry = G * lw;
-        G *= CE[j];
-    }
-    {
-        const double t0 = tau[0], c = t0 / (tau[1] - t0);
-        G += hw * v[0];
-        out[0] += carry + G * (CO[0] + c * CL[0]);
-        out[1] -= G * c * CL[0];
-    }
-}
-
-// Adds to gt direction m's tau terms of the VJP of J(S, tau) for the cotangent u.  IS holds I+ of
-// S on entry and I- of S on exit.
-__device__ inline void sc_lambda_tau_vjp_mu(int D, const Col& tau, const Col& S, const Col& u, int m, const Col& CE,
-                                            const Col& CO, const Col& CL, const Col& IS, const Col& gt) {
-    const double mu = sc_mu(m), hw = sc_hw(m);
-    // outward: reverse sweep from the surface over the stored I+
-    double G = 0.0;
-    for (int j = 0; j < D - 1; ++j) {
-        const double Sj = S[j], Sn = S[j + 1];
-        G += hw * u[j];
-        const double e = CE[j + 1], dlw = sc_dlw(e, CL[j + 1], (tau[j + 1] - tau[j]) / mu);
-        const double gx = G * (-IS[j + 1] * e + Sj * e + (Sn - Sj) * dlw) / mu;
-        G *= e;
-        gt[j + 1] += gx;
-        gt[j] -= gx;
-    }
-    {
-        const double dS = S[D - 1] - S[D - 2], dt = tau[D - 1] - tau[D - 2];
-        G += hw * u[D - 1];
-        const double gd = G * (-mu * dS / (dt * dt));
-        gt[D - 1] += gd;
-        gt[D - 2] -= gd;
-    }
-    // inward: profiles, then the reverse sweep from the deepest layer
-    sc_in_mu(D, tau, S, CE, CO, CL, IS);
-    G = 0.0;
-    for (int j = D - 1; j >= 1; --j) {
-        const double Sj = S[j], Sp = S[j - 1];
-        G += hw * u[j];
-        const double e = CE[j], dlw = sc_dlw(e, CL[j], (tau[j] - tau[j - 1]) / mu);
-        const double gx = G * (-IS[j - 1] * e + Sj * e + (Sp - Sj) * dlw) / mu;
-        G *= e;
-        gt[j] += gx;
-        gt[j - 1] -= gx;
-    }
-    {
-        const double t0 = tau[0], S0 = S[0];
-        const double S_top = S0 - t0 * (S[1] - S0) / (tau[1] - t0);
-        double d0, d1;
-        sc_top_dtau(tau, S, d0, d1);
-        G += hw * u[0];
-        const double e = CE[0], lw = CL[0], dlw = sc_dlw(e, lw, t0 / mu);
-        gt[0] += G * (S0 * e + (S_top - S0) * dlw) / mu + G * lw * d0;
-        gt[1] += G * lw * d1;
-    }
-}
-
-// Backward of the total branch for 64 pixels: a workgroup of 64 x 3 threads,
-// threadIdx.y = m the ray direction (called by every thread: it synchronises
-// the workgroup).  Needs the forward's tau, eps, S*, Lambda* and segment tables
-// of the total branch; writes dL/dkappa_line into gk.  A pixel's adjoint
-// iteration stops at max_j |d lambda_j| <= tol max_j |lambda_j| or the cap.
-__device__ inline void dev_reverse_scatter(const StarDev& s, int i) {
-    __shared__ double red[2][3][64];
-    __shared__ int done[64];
-    const int tx = threadIdx.x, m = threadIdx.y, D = s.D;
+// Backward of the total branch at pixel i, one row of lanes: needs the
+// forward's S*; writes dL/dkappa_line into gk.  The adjoint iteration stops at
+// max_j |d lambda_j| <= tol max_j |lambda_j| or the cap.
+template <int NP>
+__device__ __forceinline__ void dev_reverse_scatter(const StarDev& s, int i) {
     const bool px = i < s.N;
-    const Col B = sc_bcol(s, 0, SC_B, i), tau = sc_bcol(s, 0, SC_TAU, i), eps = sc_bcol(s, 0, SC_EPS, i),
-              S = sc_bcol(s, 0, SC_S, i), Ld = sc_bcol(s, 0, SC_LD, i);
-    const Col CE = sc_bcol(s, 0, SC_CE + m, i), CO = sc_bcol(s, 0, SC_CO + m, i), CL = sc_bcol(s, 0, SC_CL + m, i);
-    const Col lam = sc_col(s, SC_LAM, i), rhs = sc_col(s, SC_RHS, i), IS = sc_col(s, SC_IS + m, i);
-    // per-direction parts: Lambda^T (1 - eps) lambda, dF/dS G, tau terms (continuum-branch columns)
-    // and J* (the total branch's own J parts)
-    const Col U = sc_bcol(s, 1, SC_S, i);
-    const Col Tm[3] = {sc_bcol(s, 1, SC_JM, i), sc_bcol(s, 1, SC_JM + 1, i), sc_bcol(s, 1, SC_JM + 2, i)};
-    const Col gS[3] = {sc_bcol(s, 1, SC_CE, i), sc_bcol(s, 1, SC_CE + 1, i), sc_bcol(s, 1, SC_CE + 2, i)};
-    const Col gt[3] = {sc_bcol(s, 1, SC_CO, i), sc_bcol(s, 1, SC_CO + 1, i), sc_bcol(s, 1, SC_CO + 2, i)};
-    const Col Jm[3] = {sc_bcol(s, 0, SC_JM, i), sc_bcol(s, 0, SC_JM + 1, i), sc_bcol(s, 0, SC_JM + 2, i)};
-    if (px) sc_flux_vjp_mu(D, tau, S, (double)s.dLdF[i], m, CE, CO, CL, IS, gS[m], gt[m]);
-    if (m == 0) done[tx] = px ? 0 : 1;
-    __syncthreads();
-    if (px) {
-        for (int j = m; j < D; j += 3) {
-            const double r = gS[0][j] + gS[1][j] + gS[2][j];
-            rhs[j] = r;
-            lam[j] = r;
-            U[j] = (1.0 - eps[j]) * r;
+    i = min(i, s.N - 1);
+    ScPixel<NP> x;
+    double B[NP], S[NP];
+    x.setup(s, i, 0, B);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) S[k] = sc_source(s, i)[min(x.depth(k), x.D - 1)];
+    const double Gseed = s.dLdF[i];
+    const double prev = shr<1>(S[NP - 1]);
+    // direct flux terms: dF/dS G into lam (the right-hand side), tau terms of the surface slab
+    double rhs[NP], back = 0.0, top0 = 0.0, top1 = 0.0, src[3];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) rhs[k] = 0.0;
+    const double dt01 = x.dt[1], sig = (S[1] - S[0]) / dt01, t0 = x.dt[0], S_top = S[0] - t0 * sig;
+    const double d0 = -sig - t0 * sig / dt01, d1 = t0 * sig / dt01;   // dS_top / dtau_0, dtau_1 (lane 0)
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        const double mu = sc_mu(m), g0 = Gseed * 2.0 * PI * 2.0 * sc_hw(m) * mu;      // dL/dI(0, mu_m)
+        src[m] = 0.0;
+        if (x.q == 0) {
+            const ExpTerms64 t = exp_terms64(t0 / mu);
+            const double gStop = g0 * (t.om - t.lw);
+            src[m] = g0 * t.e;                            // dL/dI+(tau_0)
+            top0 += g0 * (S_top * t.e + (S[0] - S_top) * (t.e - t.lw * mu / t0)) / mu + gStop * d0;
+            top1 += gStop * d1;
+            rhs[0] += g0 * t.lw + gStop * (1.0 + t0 / dt01);
+            rhs[1] += gStop * (-t0 / dt01);
         }
+        double v[NP], G[NP], in;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) v[k] = 0.0;
+        v[0] = src[m];
+        x.adjoint_down(m, v, G, in);
+        x.outward_T(m, G, in, rhs, back);
     }
-    __syncthreads();
+    rhs[NP - 1] += shl<1>(back);
     // adjoint fixed point: lambda = rhs + Lambda^T ((1 - eps) lambda)
-    int it = 0;
-    for (;;) {
-        const bool active = px && !done[tx];
-        if (active) sc_lambda_T_mu(D, tau, U, Tm[m], m, CE, CO, CL);
-        __syncthreads();
-        double dmax = 0.0, lmax = 0.0;
-        if (active) {
-            for (int j = m; j < D; j += 3) {
-                const double e = eps[j], lj = lam[j];
-                const double T = Tm[0][j] + Tm[1][j] + Tm[2][j];
-                const double ln = lj + (rhs[j] + T - lj) / (1.0 - (1.0 - e) * Ld[j]);
-                dmax = fmax(dmax, fabs(ln - lj));
-                lmax = fmax(lmax, fabs(ln));
-                lam[j] = ln;
-                U[j] = (1.0 - e) * ln;
+    double lam[NP], U[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        if (x.depth(k) >= x.D) rhs[k] = 0.0;
+        lam[k] = rhs[k];
+        U[k] = (1.0 - x.eps[k]) * lam[k];
+    }
+    bool active = true;
+    int iters = 0;
+    for (int it = 1;; ++it) {
+        double T[NP], dmax = 0.0, lmax = 0.0;
+        x.lambda_T(U, T);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const double ln = x.depth(k) < x.D ? lam[k] + (rhs[k] + T[k] - lam[k]) * x.inv[k] : 0.0;
+            dmax = fmax(dmax, fabs(ln - lam[k]));
+            lmax = fmax(lmax, fabs(ln));
+            if (active) {
+                lam[k] = ln;
+                U[k] = (1.0 - x.eps[k]) * ln;
             }
         }
-        red[0][m][tx] = dmax;
-        red[1][m][tx] = lmax;
-        ++it;
-        __syncthreads();
-        if (m == 0 && active) {
-            const double d = fmax(red[0][0][tx], fmax(red[0][1][tx], red[0][2][tx]));
-            const double l = fmax(red[1][0][tx], fmax(red[1][1][tx], red[1][2][tx]));
-            if (d <= s.sc_tol * l || it >= s.sc_max_iter) {
-                done[tx] = 1;
-                if (s.sc_iters) s.sc_iters[2 * s.Npad + i] = it;
-            }
+        dmax = row_max(dmax);
+        lmax = row_max(lmax);
+        if (active && (dmax <= s.sc_tol * lmax || it >= s.sc_max_iter)) {
+            active = false;
+            iters = it;
         }
-        __syncthreads();
-        if (!__syncthreads_or(!done[tx])) break;
+        if (!wave_any(active)) break;
     }
-    // J* and the tau terms of the fixed point, per direction
-    if (px) {
-        sc_lambda_mu(D, tau, S, Jm[m], m, CE, CO, CL);
-        sc_lambda_tau_vjp_mu(D, tau, S, U, m, CE, CO, CL, IS, gt[m]);
+    // J* and the tau terms of the fixed point and of the flux
+    double gt[NP], J[NP];
+    back = 0.0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) gt[k] = J[k] = 0.0;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        const double mu = sc_mu(m), hw = sc_hw(m), imu = 1.0 / mu;
+        double Ip[NP], Im[NP], v[NP], G[NP], in;
+        x.outward(m, S, prev, Ip);
+        x.inward(m, S, prev, Im);
+        const double Im_above = shr<1>(Im[NP - 1]);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            J[k] += hw * (Ip[k] + Im[k]);
+            v[k] = hw * U[k];
+        }
+        if (x.q == 0) {
+            top0 -= src[m] * Ip[0] * imu;
+            v[0] += src[m];
+        }
+        // outward: G_{j-1} enters segment j
+        x.adjoint_down(m, v, G, in);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            if (k == 0 && x.q == 0) continue;
+            const double Sa = k ? S[k - 1] : prev, dlw = x.e[m][k] - x.w[m][k] * mu / x.dt[k];
+            const double gx = x.depth(k) < x.D
+                                  ? (k ? G[k - 1] : in) * (x.e[m][k] * (Sa - Ip[k]) + (S[k] - Sa) * dlw) * imu
+                                  : 0.0;
+            gt[k] += gx;
+            if (k)
+                gt[k - 1] -= gx;
+            else
+                back -= gx;
+        }
+        if (x.last) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k)
+                if (k == x.kd) {
+                    const double dS = S[k] - (k ? S[k - 1] : prev);
+                    const double g = G[k] * (-mu * dS * x.gd * x.gd);
+                    gt[k] += g;
+                    if (k)
+                        gt[k - 1] -= g;
+                    else
+                        back -= g;
+                }
+        }
+        // inward: G_j leaves segment j
+#pragma unroll
+        for (int k = 0; k < NP; ++k) v[k] = hw * U[k];
+        x.adjoint_up(m, v, G);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            if (k == 0 && x.q == 0) {
+                const ExpTerms64 t = exp_terms64(t0 * imu);
+                top0 += G[0] * ((S[0] * t.e + (S_top - S[0]) * (t.e - t.lw * mu / t0)) * imu + t.lw * d0);
+                top1 += G[0] * t.lw * d1;
+                continue;
+            }
+            const double Sa = k ? S[k - 1] : prev, dlw = x.e[m][k] - x.w[m][k] * mu / x.dt[k];
+            const double gx = x.depth(k) < x.D
+                                  ? G[k] * (x.e[m][k] * (S[k] - (k ? Im[k - 1] : Im_above)) + (Sa - S[k]) * dlw) * imu
+                                  : 0.0;
+            gt[k] += gx;
+            if (k)
+                gt[k - 1] -= gx;
+            else
+                back -= gx;
+        }
     }
-    __syncthreads();
-    if (!px || m != 0) return;
-    // dL/dchi by the trapezoid adjoint, then dL/dkappa_line
-    const ScPixel p = sc_pixel(s, i);
-    const float* kl = s.kappa + i;
-    float* out = s.gk + i;
-    double suffix = 0.0, gnext = 0.0;
-    for (int j = D - 1; j >= 0; --j) {
-        suffix += gt[0][j] + gt[1][j] + gt[2][j];
-        double gchi = (j == D - 1) ? 0.0 : 0.5 * (s.m[j + 1] - s.m[j]) * gnext;
-        gchi += (j == 0) ? s.m[0] * suffix : 0.5 * (s.m[j] - s.m[j - 1]) * suffix;
-        gnext = suffix;
-        const double sig = s.sigma_c[j] * p.fs;
-        const double chi = p.kc + (double)kl[(size_t)j * s.Npad] + sig;
-        const double geps = lam[j] * (B[j] - (Jm[0][j] + Jm[1][j] + Jm[2][j]));
-        out[(size_t)j * s.Npad] = (float)(gchi + geps * sig / (chi * chi));
+    gt[NP - 1] += shl<1>(back);
+    if (x.q == 0) {
+        gt[0] += top0;
+        gt[1] += top1;
+    }
+    // dL/dchi by the trapezoid adjoint: suffix sums of dL/dtau over the lanes below, then within
+    double a = 0.0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        if (x.depth(k) >= x.D) gt[k] = 0.0;
+        a += gt[k];
+    }
+    double r = a;
+    r += shl<1>(r);
+    r += shl<2>(r);
+    r += shl<4>(r);
+    r += shl<8>(r);
+    double next = shl<1>(r);                              // Gamma below the lane's last depth
+    if (x.q == 0 && px && s.sc_iters) s.sc_iters[2 * s.Npad + i] = iters;
+#pragma unroll
+    for (int k = NP - 1; k >= 0; --k) {
+        const int j = x.depth(k), jc = min(j, x.D - 1);
+        const double suffix = next + gt[k];
+        double g = jc + 1 < x.D ? 0.5 * (s.m[jc + 1] - s.m[jc]) * next : 0.0;
+        g += jc == 0 ? s.m[0] * suffix : 0.5 * (s.m[jc] - s.m[jc - 1]) * suffix;
+        next = suffix;
+        const double sg = s.sigma_c[jc] * x.fs;
+        const double geps = lam[k] * (B[k] - J[k]);
+        if (px && j < x.D) s.gk[(size_t)j * s.Npad + i] = (float)(g + geps * sg / (x.chi[k] * x.chi[k]));
     }
 }
 
