@@ -519,6 +519,8 @@ StarDev make_star(const pz_plan* p, const pz_atmos* atm, const pz_params* par) {
     s.quad = p->quadrature;
     s.lam_first_nm = p->lam_first_nm;
     s.h = p->h;
+    s.ln_first = std::log(p->lam_first_nm);
+    s.ln_ref = std::log(atm->lam_ref_nm);
     s.h_hi = (float)p->h;
     s.h_lo = (float)(p->h - (double)s.h_hi);
     s.ln = p->ln;

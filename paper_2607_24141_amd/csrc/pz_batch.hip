@@ -35,10 +35,10 @@ enum Phase {
     PH_SPLIT,      // (star, 32-pixel tile) of stars with split sums, decreasing cost
     PH_FAR2,       // (star, 32-pixel tile): far zone of stars with short grids
     PH_FAR4,       // (star, 64-pixel tile): ... with long ones
-    PH_FLUX,       // (star, 512 pixels)
     PH_SEED,       // (star, 512 pixels): chi^2 seed for stars with a target
     PH_LOSS,       // (star): chi^2 value, one 1024-thread workgroup
-    PH_REVERSE,    // (star, 64 pixels), 64-thread workgroups
+    PH_ROWS,       // (star, ROW_ITEM pixels): transfer, one list for each row_list()
+    PH_ROWS_END = PH_ROWS + 7,
     PH_GATHER,     // (star, GATHER_ITEM lines), atomic queue
     PH_GSPLIT,     // (star, GATHER_ITEM lines) of stars with split sums
     PH_SCATTER,    // (star, 512 lines)
@@ -50,6 +50,8 @@ enum Phase {
 constexpr int PARAM_ITEM = 512 * 32;
 constexpr int N_COUNTER = 4;             // queues: opacity x 3 tile widths, gather
 constexpr int GATHER_ITEM = 64;
+constexpr int ROW_ITEM = 64;             // pixels of a transfer item: four passes of 16
+int row_list(const pz::StarDev& s) { return PH_ROWS + 2 * (pz::row_np(s.D) - 2) + (s.quad == PZ_QUAD_E2); }
 
 // Next item of an atomic queue for the whole workgroup (wavefront-uniform).
 __device__ __forceinline__ int next_item(int* ctr, int* s_it) {
@@ -159,16 +161,32 @@ __global__ __launch_bounds__(256) void kb_opacity_near(const StarDev* __restrict
         dev_opacity_near<NEAR_G, false>(s, w.y, blockIdx.y, near_tab, pw);
 }
 
-__global__ __launch_bounds__(512) void kb_flux(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n) {
-    for (int it = blockIdx.x; it < n; it += gridDim.x) {
-        const int2 w = uniform_item(items, it);
-        const StarDev& s = stars[w.x];
-        const int i = w.y * 512 + threadIdx.x;
-        if (s.quad == PZ_QUAD_E2)
-            dev_flux_e2<true, true>(s, i, GlobalKCol{s.kappa + i, (size_t)s.Npad});
+// Transfer (REV: its adjoint) of the stars with NP depths per lane and one
+// quadrature: a kernel for all of them would take the registers of the largest
+// everywhere (254, one wavefront per SIMD): the adjoint of eight stars took
+// 0.36 ms so, 0.33 by one thread per pixel, and takes 0.24.
+template <int NP, bool E2, bool REV>
+__global__ __launch_bounds__(256) void kb_rows(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    const int2 w = uniform_item(items, blockIdx.x);
+    const StarDev& s = stars[w.x];
+#pragma unroll 1
+    for (int k = 0; k < ROW_ITEM; k += 16) {
+        const int i = w.y * ROW_ITEM + k + threadIdx.x / 16;
+        if constexpr (REV && E2)
+            dev_reverse_e2_row<NP>(s, i);
+        else if constexpr (REV)
+            dev_reverse_row<NP>(s, i);
         else
-            dev_flux<true, true>(s, i, GlobalKCol{s.kappa + i, (size_t)s.Npad});
+            dev_flux_e2_row<NP>(s, i);
     }
+}
+
+__global__ __launch_bounds__(256) void kb_flux(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ FluxLds lds;
+    const int2 w = uniform_item(items, blockIdx.x);
+    const StarDev& s = stars[w.x];
+#pragma unroll 1
+    for (int k = w.y * ROW_ITEM; k < min((w.y + 1) * ROW_ITEM, s.N); k += FLUX_PX) dev_flux_block(s, k, lds);
 }
 
 __global__ __launch_bounds__(512) void kb_seed(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n, const float* inv_s2,
@@ -189,22 +207,6 @@ __global__ __launch_bounds__(1024) void kb_loss(const StarDev* __restrict__ star
         const StarDev& s = stars[w.x];
         dev_chi2_loss(s.N, s.F, s.Fc, ys[w.x], inv_s2[w.x], losses[w.x], red);
         __syncthreads();
-    }
-}
-
-__global__ __launch_bounds__(64) void kb_reverse(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n) {
-    __shared__ double col[MAXD * WAVE];               // each thread's own column
-    for (int it = blockIdx.x; it < n; it += gridDim.x) {
-        const int2 w = uniform_item(items, it);
-        const StarDev& s = stars[w.x];
-        const int i = w.y * 64 + threadIdx.x;
-        if (s.quad == PZ_QUAD_E2) {
-            if (i < s.N) stage_kappa_column64(s, i, col + threadIdx.x);
-            dev_reverse_scan_e2(s, i, col + threadIdx.x);
-        } else {
-            if (i < s.N) stage_kappa_column64(s, i, col + threadIdx.x);
-            dev_reverse_scan(s, i, col + threadIdx.x);
-        }
     }
 }
 
@@ -315,7 +317,7 @@ struct pz_batch {
     const float** ys;
     float** losses;
     int* ctr;             // [N_COUNTER] queue counters: opacity (32, 64, 128), gather
-    int grid512, grid256, grid1024, grid_op[3], grid_gather, grid_rev;
+    int grid512, grid256, grid1024, grid_op[3], grid_gather;
     void* base;
 };
 
@@ -362,6 +364,21 @@ static void batch_opacity(const pz_batch* bt, hipStream_t st) {
         batch_opacity_wpx<8, ANYCT>(bt, n[PH_OP64], it[PH_OP64], bt->ctr + 1, grid(bt->grid_op[1], n[PH_OP64]), st);
     if (n[PH_OP128])
         batch_opacity_wpx<16, ANYCT>(bt, n[PH_OP128], it[PH_OP128], bt->ctr + 2, grid(bt->grid_op[2], n[PH_OP128]), st);
+}
+
+template <bool REV>
+static void batch_rows(const pz_batch* bt, hipStream_t st) {
+    for (int np = 2; np <= 5; ++np)
+        with_row_np(16 * np, [&](auto NP) {
+            const int g = PH_ROWS + 2 * (np - 2), e = g + 1;
+            if (bt->n_items[g]) {
+                if constexpr (REV)
+                    kb_rows<NP.value, false, true><<<bt->n_items[g], 256, 0, st>>>(bt->stars, bt->items[g]);
+                else
+                    kb_flux<<<bt->n_items[g], 256, 0, st>>>(bt->stars, bt->items[g]);
+            }
+            if (bt->n_items[e]) kb_rows<NP.value, true, REV><<<bt->n_items[e], 256, 0, st>>>(bt->stars, bt->items[e]);
+        });
 }
 
 extern "C" {
@@ -416,12 +433,10 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
             for (int t = 0; t < (wide ? (s.n_t32 + 1) / 2 : s.n_t32); ++t) items[wide ? PH_FAR4 : PH_FAR2].push_back({b, t});
         }
         // a star with scattering runs its transfer and reverse transfer in launches of its own
-        for (int k = 0; k < (s.N + 511) / 512; ++k) {
-            if (!s.scatter) items[PH_FLUX].push_back({b, k});
-            if (st.y) items[PH_SEED].push_back({b, k});
-        }
+        if (st.y)
+            for (int k = 0; k < (s.N + 511) / 512; ++k) items[PH_SEED].push_back({b, k});
         if (!s.scatter)
-            for (int k = 0; k < (s.N + 63) / 64; ++k) items[PH_REVERSE].push_back({b, k});
+            for (int k = 0; k < (s.N + ROW_ITEM - 1) / ROW_ITEM; ++k) items[row_list(s)].push_back({b, k});
         if (st.y && st.loss) items[PH_LOSS].push_back({b, 0});
         for (int k = 0; k < (s.L + GATHER_ITEM - 1) / GATHER_ITEM; ++k) items[s.split_gather ? PH_GSPLIT : PH_GATHER].push_back({b, k});
         for (int k = 0; k < (s.L + 511) / 512; ++k) items[PH_SCATTER].push_back({b, k});
@@ -495,7 +510,6 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
     bt->grid512 = std::max(1, n_cu * 4);
     bt->grid256 = std::max(1, n_cu * 8);
     bt->grid1024 = std::max(1, n_cu * 2);
-    bt->grid_rev = std::max(1, n_cu * 16);
     bt->plans.reserve(n_star);
     for (int b = 0; b < n_star; ++b) bt->plans.push_back(stars[b].plan);
     for (int b = 0; b < n_star; ++b)
@@ -531,7 +545,7 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
         batch_opacity<true>(bt, st);
     else
         batch_opacity<false>(bt, st);
-    if (n[PH_FLUX]) kb_flux<<<grid(bt->grid512, n[PH_FLUX]), 512, 0, st>>>(bt->stars, it[PH_FLUX], n[PH_FLUX]);
+    batch_rows<false>(bt, st);
     for (const StarDev& s : bt->sc_stars) {
         const hipError_t e = launch_flux(s, st);
         if (e != hipSuccess) return set_error(PZ_E_HIP, hipGetErrorString(e));
@@ -542,8 +556,7 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
         kb_loss<<<grid(bt->grid1024, n[PH_LOSS]), 1024, 0, st>>>(bt->stars, it[PH_LOSS], n[PH_LOSS], bt->inv_s2,
                                                                  bt->ys, bt->losses);
     if (mode == PZ_MODE_FWD_BWD) {
-        if (n[PH_REVERSE])
-            kb_reverse<<<grid(bt->grid_rev, n[PH_REVERSE]), 64, 0, st>>>(bt->stars, it[PH_REVERSE], n[PH_REVERSE]);
+        batch_rows<true>(bt, st);
         for (const StarDev& s : bt->sc_stars) {
             const hipError_t e = launch_reverse_scan(s, st);
             if (e != hipSuccess) return set_error(PZ_E_HIP, hipGetErrorString(e));

@@ -43,6 +43,7 @@ struct StarDev {
     // grid
     int N, Npad, L, S, D, tile_px, n_tiles, chunk, quad;
     double lam_first_nm, h;      // h = ln(1 + 1/R)
+    double ln_first, ln_ref;     // ln of lam_first_nm and of the atmosphere's lam_ref_nm
     float h_hi, h_lo;            // h split for float32 offsets
     LineArrays ln;
     const int* tile_first;       // [n_tiles]

@@ -99,29 +99,25 @@ int opacity_grid(int tile_px, bool center) {
     return n_cu * occ;
 }
 
-// blockIdx.y = 0: the total branch, from an LDS copy of the pixel's
-// kappa_line column; blockIdx.y = 1: the continuum branch (reads no kappa_line).
-__global__ __launch_bounds__(64) void k_flux(StarDev s) {
-    __shared__ float kst[MAXD * WAVE];
-    const int i = blockIdx.x * WAVE + threadIdx.x;
-    if (blockIdx.y == 0) {
-        if (i < s.N) stage_kappa_column(s, i, kst + threadIdx.x);
-        dev_flux<true, false>(s, i, LdsKCol{kst + threadIdx.x});
-    } else {
-        dev_flux<false, true>(s, i, GlobalKCol{s.kappa + i, (size_t)s.Npad});
-    }
+__global__ __launch_bounds__(256) void k_flux(StarDev s) {
+    __shared__ FluxLds lds;
+    dev_flux_block(s, blockIdx.x * FLUX_PX, lds);
 }
 
-// As k_flux, with the exact E2 angle integral in float64.
-__global__ __launch_bounds__(64) void k_flux_e2(StarDev s) {
-    __shared__ float kst[MAXD * WAVE];
-    const int i = blockIdx.x * WAVE + threadIdx.x;
-    if (blockIdx.y == 0) {
-        if (i < s.N) stage_kappa_column(s, i, kst + threadIdx.x);
-        dev_flux_e2<true, false>(s, i, LdsKCol{kst + threadIdx.x});
-    } else {
-        dev_flux_e2<false, true>(s, i, GlobalKCol{s.kappa + i, (size_t)s.Npad});
-    }
+// Sixteen lanes per pixel, 16 pixels per workgroup.
+template <int NP>
+__global__ __launch_bounds__(256) void k_flux_e2(StarDev s) {
+    dev_flux_e2_row<NP>(s, blockIdx.x * 16 + threadIdx.x / 16);
+}
+
+template <int NP>
+__global__ __launch_bounds__(256) void k_reverse_scan(StarDev s) {
+    dev_reverse_row<NP>(s, blockIdx.x * 16 + threadIdx.x / 16);
+}
+
+template <int NP>
+__global__ __launch_bounds__(256) void k_reverse_scan_e2(StarDev s) {
+    dev_reverse_e2_row<NP>(s, blockIdx.x * 16 + threadIdx.x / 16);
 }
 
 // Sixteen lanes per pixel, 16 pixels per workgroup; blockIdx.y: the branch.
@@ -134,6 +130,61 @@ template <int NP>
 __global__ __launch_bounds__(256) void k_reverse_scatter(StarDev s) {
     dev_reverse_scatter<NP>(s, blockIdx.x * 16 + threadIdx.x / 16);
 }
+
+// The formal solutions walked by one thread, for a single column: the same
+// segments, in the same order, as dev_flux_block and dev_flux_e2_row.
+struct Ray3 {
+    float F[3], A[3];
+    __device__ void top(float S0, float S1, float t0, float t1) {
+        const float S_top = S0 - t0 * (S1 - S0) / (t1 - t0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const ExpTerms et = exp_terms(t0 * c_inv_mu[k], false);
+            F[k] = fmaf(S_top, et.om, (S0 - S_top) * et.lw);
+            A[k] = et.e;
+        }
+    }
+    __device__ void seg(float Sa, float Sb, float ta, float tb) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const ExpTerms et = exp_terms((tb - ta) * c_inv_mu[k], false);
+            const float c = fmaf(Sa, et.om, (Sb - Sa) * et.lw);
+            F[k] = fmaf(A[k], c, F[k]);
+            A[k] *= et.e;
+        }
+    }
+    __device__ float bottom(float Sa, float Sb, float ta, float tb) {
+        const float grad = (Sb - Sa) / (tb - ta);
+        float out = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float ID = fmaf(c_mu[k], grad, Sb);
+            out = fmaf(c_wmu[k], fmaf(A[k], ID, F[k]), out);
+        }
+        return out;
+    }
+};
+
+struct RayE2 {
+    double F, E3a, E4a;
+    __device__ void start() {
+        F = 0.0;
+        E3a = 0.5;            // E3(0)
+        E4a = 1.0 / 3.0;      // E4(0)
+    }
+    __device__ void seg(double Sa, double Sb, double ta, double tb) {
+        double E3b, E4b;
+        expint34(tb, E3b, E4b);
+        const double sl = (Sb - Sa) / (tb - ta);
+        F += Sa * (E3a - E3b) + sl * (E4a - E4b - (tb - ta) * E3b);
+        E3a = E3b;
+        E4a = E4b;
+    }
+    __device__ double bottom(double Sa, double Sb, double ta, double tb) const {
+        const double sD = (Sb - Sa) / (tb - ta);
+        return 2.0 * PI * (F + Sb * E3a + sD * E4a);
+    }
+};
 
 __global__ void k_debug_formal(int D, int n, const float* S, const float* tau, int quad, float* F) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -169,21 +220,6 @@ __global__ void k_debug_formal(int D, int n, const float* S, const float* tau, i
         r.seg(Sa, Sb, ta, tb);
     }
     F[i] = r.bottom(Sa, Sb, ta, tb);
-}
-
-// One thread per pixel; its float64 column in LDS holds kappa_line, then dL/dtau.
-__global__ __launch_bounds__(64) void k_reverse_scan(StarDev s) {
-    __shared__ double col[MAXD * WAVE];
-    const int i = blockIdx.x * WAVE + threadIdx.x;
-    if (i < s.N) stage_kappa_column64(s, i, col + threadIdx.x);
-    dev_reverse_scan(s, i, col + threadIdx.x);
-}
-
-__global__ __launch_bounds__(64) void k_reverse_scan_e2(StarDev s) {
-    __shared__ double col[MAXD * WAVE];
-    const int i = blockIdx.x * WAVE + threadIdx.x;
-    if (i < s.N) stage_kappa_column64(s, i, col + threadIdx.x);
-    dev_reverse_scan_e2(s, i, col + threadIdx.x);
 }
 
 // Workgroups are dealt to the eight XCDs in turn (workgroup b to XCD b mod 8).
@@ -315,45 +351,29 @@ hipError_t launch_opacity(const StarDev& s, int chunk, hipStream_t st) {
     return s.center ? launch_opacity_tiles<true>(s, chunk, grid, st) : launch_opacity_tiles<false>(s, chunk, grid, st);
 }
 
-// NP depths per lane: the fewest that cover D on sixteen lanes (at least two,
-// so that lane 0 holds both depths of the surface extrapolation).
-template <int NP>
-static void launch_scatter_np(const StarDev& s, bool reverse, hipStream_t st) {
-    const unsigned n = (s.N + 15) / 16;
-    if (reverse)
-        k_reverse_scatter<NP><<<n, 256, 0, st>>>(s);
-    else
-        k_flux_scatter<NP><<<dim3(n, 2), 256, 0, st>>>(s);
-}
-
-static void launch_scatter(const StarDev& s, bool reverse, hipStream_t st) {
-    static_assert(MAXD <= 80, "five depths per lane");
-    switch ((s.D + 15) / 16) {
-        case 1:
-        case 2: launch_scatter_np<2>(s, reverse, st); break;
-        case 3: launch_scatter_np<3>(s, reverse, st); break;
-        case 4: launch_scatter_np<4>(s, reverse, st); break;
-        default: launch_scatter_np<5>(s, reverse, st); break;
-    }
-}
-
 hipError_t launch_flux(const StarDev& s, hipStream_t st) {
-    if (s.scatter)
-        launch_scatter(s, false, st);
-    else if (s.quad == PZ_QUAD_E2)
-        k_flux_e2<<<dim3((s.N + WAVE - 1) / WAVE, 2), WAVE, 0, st>>>(s);
-    else
-        k_flux<<<dim3((s.N + WAVE - 1) / WAVE, 2), WAVE, 0, st>>>(s);
+    const unsigned n = (s.N + 15) / 16;
+    with_row_np(s.D, [&](auto np) {
+        if (s.scatter)
+            k_flux_scatter<np.value><<<dim3(n, 2), 256, 0, st>>>(s);
+        else if (s.quad == PZ_QUAD_E2)
+            k_flux_e2<np.value><<<n, 256, 0, st>>>(s);
+        else
+            k_flux<<<n, 256, 0, st>>>(s);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_reverse_scan(const StarDev& s, hipStream_t st) {
-    if (s.scatter)
-        launch_scatter(s, true, st);
-    else if (s.quad == PZ_QUAD_E2)
-        k_reverse_scan_e2<<<(s.N + 63) / 64, 64, 0, st>>>(s);
-    else
-        k_reverse_scan<<<(s.N + 63) / 64, 64, 0, st>>>(s);
+    const unsigned n = (s.N + 15) / 16;
+    with_row_np(s.D, [&](auto np) {
+        if (s.scatter)
+            k_reverse_scatter<np.value><<<n, 256, 0, st>>>(s);
+        else if (s.quad == PZ_QUAD_E2)
+            k_reverse_scan_e2<np.value><<<n, 256, 0, st>>>(s);
+        else
+            k_reverse_scan<np.value><<<n, 256, 0, st>>>(s);
+    });
     return hipGetLastError();
 }
 

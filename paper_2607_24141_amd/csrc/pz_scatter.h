@@ -34,8 +34,9 @@
 // The iteration so touches no memory: with one thread per (pixel, direction)
 // and the segment coefficients in tables it moved 10.6 GB per launch at
 // 37,550 pixels (2.0 ms; the adjoint 4.6 GB, 1.3 ms), bound by HBM.  What is
-// left is float64 arithmetic, most of it the exponentials of the coefficients
-// (SCATTER_FIGURES).
+// left is float64 arithmetic, most of it the exponentials of the coefficients:
+// at 20,011 pixels and 72 depths the forward takes 0.20 ms (1.18 before), the
+// adjoint 0.11 (0.95).
 // Segment j runs from depth j - 1 to j (j = 0: from the surface); with S between
 // depths linear, e = e^-x, w = lw(x) and p = 1 - e^-x - lw(x):
 //   inward   I_j     = e_j I_{j-1} + p_j S_j + w_j S_{j-1},
@@ -46,37 +47,6 @@ namespace pz {
 
 __device__ __forceinline__ double sc_mu(int k) { return k == 0 ? kMu0 : (k == 1 ? kMu1 : kMu2); }
 __device__ __forceinline__ double sc_hw(int k) { return k == 1 ? 0.5 * 8.0 / 18.0 : 0.5 * 5.0 / 18.0; }   // w_k / 2
-
-// Row shifts of a float64 (zero enters): shr<n> takes the value n lanes below,
-// shl<n> n lanes above, within the row of 16.
-template <int CTRL>
-__device__ __forceinline__ double row_move(double x) {
-    const unsigned long long u = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-template <int n>
-__device__ __forceinline__ double shr(double x) { return row_move<0x110 + n>(x); }
-template <int n>
-__device__ __forceinline__ double shl(double x) { return row_move<0x100 + n>(x); }
-
-// Sum and maximum over the row, the same value in every lane (a fixed order).
-__device__ __forceinline__ double row_sum(double x) {
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) x += __shfl_xor(x, o, WAVE);
-    return x;
-}
-__device__ __forceinline__ double row_max(double x) {
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) x = fmax(x, __shfl_xor(x, o, WAVE));
-    return x;
-}
-// Whether every lane of this lane's row holds c.
-__device__ __forceinline__ bool row_all(bool c) {
-    const unsigned long long b = __builtin_amdgcn_ballot_w64(!c);
-    return ((b >> (threadIdx.x & 48)) & 0xffffull) == 0;
-}
 
 // One branch of one pixel, spread over its row.
 template <int NP>
@@ -612,30 +582,14 @@ __device__ __forceinline__ void dev_reverse_scatter(const StarDev& s, int i) {
         gt[0] += top0;
         gt[1] += top1;
     }
-    // dL/dchi by the trapezoid adjoint: suffix sums of dL/dtau over the lanes below, then within
-    double a = 0.0;
+    if (x.q == 0 && px && s.sc_iters) s.sc_iters[2 * s.Npad + i] = iters;
+    row_dchi<NP>(s, x.q, gt);
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        if (x.depth(k) >= x.D) gt[k] = 0.0;
-        a += gt[k];
-    }
-    double r = a;
-    r += shl<1>(r);
-    r += shl<2>(r);
-    r += shl<4>(r);
-    r += shl<8>(r);
-    double next = shl<1>(r);                              // Gamma below the lane's last depth
-    if (x.q == 0 && px && s.sc_iters) s.sc_iters[2 * s.Npad + i] = iters;
-#pragma unroll
-    for (int k = NP - 1; k >= 0; --k) {
-        const int j = x.depth(k), jc = min(j, x.D - 1);
-        const double suffix = next + gt[k];
-        double g = jc + 1 < x.D ? 0.5 * (s.m[jc + 1] - s.m[jc]) * next : 0.0;
-        g += jc == 0 ? s.m[0] * suffix : 0.5 * (s.m[jc] - s.m[jc - 1]) * suffix;
-        next = suffix;
-        const double sg = s.sigma_c[jc] * x.fs;
+        const int j = x.depth(k);
+        const double sg = s.sigma_c[min(j, x.D - 1)] * x.fs;
         const double geps = lam[k] * (B[k] - J[k]);
-        if (px && j < x.D) s.gk[(size_t)j * s.Npad + i] = (float)(g + geps * sg / (x.chi[k] * x.chi[k]));
+        if (px && j < x.D) s.gk[(size_t)j * s.Npad + i] = (float)(gt[k] + geps * sg / (x.chi[k] * x.chi[k]));
     }
 }
 

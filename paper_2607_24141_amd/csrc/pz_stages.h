@@ -6,7 +6,10 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "pz_internal.h"
+#include "pz_rows.h"
 #include "pz_voigt.h"
 
 namespace pz {
@@ -274,38 +277,6 @@ __device__ __forceinline__ ExpTerms exp_terms(float x, bool need_d) {
     return r;
 }
 
-struct Ray3 {
-    float F[3], A[3];
-    __device__ void top(float S0, float S1, float t0, float t1) {
-        const float S_top = S0 - t0 * (S1 - S0) / (t1 - t0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const ExpTerms et = exp_terms(t0 * c_inv_mu[k], false);
-            F[k] = fmaf(S_top, et.om, (S0 - S_top) * et.lw);
-            A[k] = et.e;
-        }
-    }
-    __device__ void seg(float Sa, float Sb, float ta, float tb) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const ExpTerms et = exp_terms((tb - ta) * c_inv_mu[k], false);
-            const float c = fmaf(Sa, et.om, (Sb - Sa) * et.lw);
-            F[k] = fmaf(A[k], c, F[k]);
-            A[k] *= et.e;
-        }
-    }
-    __device__ float bottom(float Sa, float Sb, float ta, float tb) {
-        const float grad = (Sb - Sa) / (tb - ta);
-        float out = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const float ID = fmaf(c_mu[k], grad, Sb);
-            out = fmaf(c_wmu[k], fmaf(A[k], ID, F[k]), out);
-        }
-        return out;
-    }
-};
-
 struct PixelSetup {
     float kc;        // continuum per unit mass
     float c1;        // 2 h c^2 / lambda^5 per nm
@@ -327,77 +298,190 @@ __device__ __forceinline__ float planck(const PixelSetup& p, float invT) {
     return p.c1 / expm1f(p.c2 * invT);
 }
 
-// A pixel's kappa_line column kappa_line[j][i], read from global memory or
-// from a copy staged in LDS (64 columns interleaved, conflict-free).
-struct GlobalKCol {
-    const float* p;
-    size_t st;
-    __device__ __forceinline__ float operator[](int j) const { return p[(size_t)j * st]; }
+// Both fluxes of the FLUX_PX pixels from i0 by a workgroup of 256, float32.
+// What costs, the exponentials of a segment on three rays and two branches, is
+// independent of the other segments and is spread over all lanes, sixteen
+// depths at a time; only the running optical depth (one lane per pixel and
+// branch) and F += A c, A *= e (one per pixel, branch and ray) walk the depths,
+// over LDS and in depth order, so that the rounding is that of a scan by one
+// thread: gradients of saturated spectra cancel to 1e-4 of their terms, and
+// another order of these sums shows in them.  One thread per pixel and branch
+// needs 72 serial steps with three rays' exponentials in each: 52 us at 1,795
+// pixels, 16 now; 53 against 41 at 20,011; 0.30 ms either way at 361,193, where
+// one lane per pixel fills the chip.
+constexpr int FLUX_PX = 16;
+struct FluxLds {
+    float kc[FLUX_PX], c1[FLUX_PX], c2[FLUX_PX];
+    float invT[MAXD], m[MAXD];
+    float S[MAXD][FLUX_PX];
+    float tau[2][MAXD][FLUX_PX];                          // tau[0] holds chi first
+    float2 t[2][3][16][FLUX_PX];                          // (c, e^-x) of sixteen segments
+    float I[2][3][FLUX_PX];
 };
-struct LdsKCol {
-    const float* p;
-    __device__ __forceinline__ float operator[](int j) const { return p[j * WAVE]; }
+__device__ __forceinline__ void dev_flux_block(const StarDev& s, int i0, FluxLds& L) {
+    const int t = threadIdx.x, px = t & 15, g = t >> 4, D = s.D, i = min(i0 + px, s.N - 1);
+    if (g == 0) {
+        const PixelSetup p = pixel_setup(s, i);
+        L.kc[px] = p.kc;
+        L.c1[px] = p.c1;
+        L.c2[px] = p.c2;
+    }
+    if (t >= 64 && t - 64 < D) {
+        L.invT[t - 64] = (float)(1.0 / s.T[t - 64]);
+        L.m[t - 64] = (float)s.m[t - 64];
+    }
+    __syncthreads();
+    const PixelSetup p = {L.kc[px], L.c1[px], L.c2[px]};
+    for (int j = g; j < D; j += 16) {
+        L.S[j][px] = planck(p, L.invT[j]);
+        L.tau[0][j][px] = p.kc + s.kappa[(size_t)j * s.Npad + i];
+    }
+    __syncthreads();
+    if (g < 2) {
+        float chi_b = g == 0 ? L.tau[0][0][px] : p.kc, tau = chi_b * L.m[0];
+        L.tau[g][0][px] = tau;
+#pragma unroll 8
+        for (int j = 1; j < D; ++j) {
+            const float chi = g == 0 ? L.tau[0][j][px] : p.kc;
+            tau = fmaf(g == 0 ? 0.5f * (chi_b + chi) : p.kc, L.m[j] - L.m[j - 1], tau);
+            L.tau[g][j][px] = tau;
+            chi_b = chi;
+        }
+    }
+    __syncthreads();
+    // lanes of the walk: (branch, ray) = g < 6
+    const int wb = g < 3 ? 0 : 1, wm = g - 3 * wb;
+    float F = 0.0f, A = 1.0f;
+    for (int j0 = 0; j0 < D; j0 += 16) {
+        const int j = j0 + g;
+        if (j < D) {
+            const float Sb = L.S[j][px];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const float tb = L.tau[b][j][px];
+                float Sa, dt;
+                if (j == 0) {                             // the slab above the first depth
+                    dt = tb;
+                    Sa = Sb - tb * (L.S[1][px] - Sb) / (L.tau[b][1][px] - tb);
+                } else {
+                    dt = tb - L.tau[b][j - 1][px];
+                    Sa = L.S[j - 1][px];
+                }
+#pragma unroll
+                for (int m = 0; m < 3; ++m) {
+                    const ExpTerms et = exp_terms(dt * c_inv_mu[m], false);
+                    L.t[b][m][g][px] = make_float2(fmaf(Sa, et.om, (Sb - Sa) * et.lw), et.e);
+                }
+            }
+        }
+        __syncthreads();
+        if (g < 6) {
+            const int n = min(16, D - j0);
+            if (j0 == 0) F = L.t[wb][wm][0][px].x, A = L.t[wb][wm][0][px].y;
+#pragma unroll 4
+            for (int k = j0 == 0; k < n; ++k) {
+                const float2 ce = L.t[wb][wm][k][px];
+                F = fmaf(A, ce.x, F);
+                A *= ce.y;
+            }
+        }
+        __syncthreads();
+    }
+    if (g < 6) {
+        const float Sa = L.S[D - 2][px], Sb = L.S[D - 1][px];
+        const float grad = (Sb - Sa) / (L.tau[wb][D - 1][px] - L.tau[wb][D - 2][px]);
+        L.I[wb][wm][px] = fmaf(A, fmaf(c_mu[wm], grad, Sb), F);
+    }
+    __syncthreads();
+    if (g < 2 && i0 + px < s.N) {
+        float out = 0.0f;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) out = fmaf(c_wmu[m], L.I[g][m][px], out);
+        (g == 0 ? s.F : s.Fc)[i] = out;
+    }
+    __syncthreads();                                      // L may be used again
+}
+
+// Float64 transfer quantities of a pixel on a row: opacity, segments, Planck function.
+template <int NP>
+struct RowPixel64 {
+    int D, q, kd;
+    bool last;
+    double kc, S[NP], S_above;                            // S_above: S above the lane's first depth (lane 0: unset)
+    double chi[NP], chi_above, dm[NP];
+
+    __device__ __forceinline__ int depth(int k) const { return q * NP + k; }
+
+    __device__ __forceinline__ void setup(const StarDev& s, int i) {
+        D = s.D;
+        q = threadIdx.x & 15;
+        kd = (D - 1) % NP;
+        last = q == (D - 1) / NP;
+        const double lnl = s.ln_first + (double)i * s.h;
+        const double lam_cm = exp(lnl) * 1.0e-7;
+        kc = s.kappa0 * exp(s.alpha * (lnl - s.ln_ref));
+        const double l2 = lam_cm * lam_cm;
+        const double c1 = 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7;
+        const double c2 = H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ);
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int j = min(depth(k), D - 1);
+            S[k] = c1 / expm1(c2 / s.T[j]);
+            chi[k] = kc + (double)s.kappa[(size_t)j * s.Npad + i];
+            dm[k] = j == 0 ? s.m[0] : s.m[j] - s.m[j - 1];
+        }
+        S_above = shr<1>(S[NP - 1]);
+        chi_above = shr<1>(chi[NP - 1]);
+    }
+    // tau_j - tau_{j-1} of the total (cont: the continuum) branch
+    __device__ __forceinline__ void segments(bool cont, double* dt) const {
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            dt[k] = cont ? kc * dm[k]
+                         : (depth(k) == 0 ? chi[0] : 0.5 * ((k ? chi[k - 1] : chi_above) + chi[k])) * dm[k];
+    }
+    // Value k = kd of an array (the last depth, in the last lane)
+    __device__ __forceinline__ double at_kd(const double* a) const {
+        double x = a[0];
+#pragma unroll
+        for (int k = 1; k < NP; ++k)
+            if (k == kd) x = a[k];
+        return x;
+    }
 };
 
-// Copies pixel i's column into col (stride WAVE): sixteen loads in flight per
-// wait instead of one per depth step.  Only the calling thread reads it back.
-__device__ __forceinline__ void stage_kappa_column(const StarDev& s, int i, float* col) {
-    const float* kl = s.kappa + i;
+// gt, dL/dtau at the lane's depths (0 past D - 1), becomes dL/dchi: the
+// trapezoid rule's adjoint through the suffix sums Gamma_j.
+template <int NP>
+__device__ __forceinline__ void row_dchi(const StarDev& s, int q, double* gt) {
     const int D = s.D;
-    for (int j0 = 0; j0 < D; j0 += 16) {
-        float v[16];
+    double r = 0.0;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = kl[(size_t)min(j0 + u, D - 1) * s.Npad];
+    for (int k = 0; k < NP; ++k) {
+        if (q * NP + k >= D) gt[k] = 0.0;
+        r += gt[k];
+    }
+    r += shl<1>(r);
+    r += shl<2>(r);
+    r += shl<4>(r);
+    r += shl<8>(r);
+    double next = shl<1>(r);                              // Gamma below the lane's last depth
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (j0 + u < D) col[(j0 + u) * WAVE] = v[u];
+    for (int k = NP - 1; k >= 0; --k) {
+        const int j = min(q * NP + k, D - 1);
+        const double suffix = next + gt[k];
+        double g = j + 1 < D ? 0.5 * (s.m[j + 1] - s.m[j]) * next : 0.0;
+        g += j == 0 ? s.m[0] * suffix : 0.5 * (s.m[j] - s.m[j - 1]) * suffix;
+        gt[k] = g;
+        next = suffix;
     }
 }
 
-// tau scan and Gauss-3 flux of pixel i on the total branch (TOT: F) and/or
-// the continuum branch (CONT: Fc); both branches share the source function.
-template <bool TOT, bool CONT, class KCol>
-__device__ __forceinline__ void dev_flux(const StarDev& s, int i, const KCol& kl) {
-    if (i >= s.N) return;
-    const PixelSetup p = pixel_setup(s, i);
-    const int D = s.D;
-    float m0 = (float)s.m[0];
-    float S0 = planck(p, (float)(1.0 / s.T[0]));
-    float chi_t = TOT ? p.kc + kl[0] : 0.0f;
-    float tt0 = chi_t * m0;
-    float tc0 = p.kc * m0;
-    float m1 = (float)s.m[1];
-    float S1 = planck(p, (float)(1.0 / s.T[1]));
-    float chi_t1 = TOT ? p.kc + kl[1] : 0.0f;
-    float tt1 = fmaf(0.5f * (chi_t + chi_t1), m1 - m0, tt0);
-    float tc1 = fmaf(p.kc, m1 - m0, tc0);
-    Ray3 rt, rc;
-    if (TOT) rt.top(S0, S1, tt0, tt1);
-    if (CONT) rc.top(S0, S1, tc0, tc1);
-    float Sa = S0, Sb = S1, ta = tt0, tb = tt1, ca = tc0, cb = tc1;
-    float chi_b = chi_t1, mb = m1;
-    for (int j = 1; j < D; ++j) {
-        if (j > 1) {
-            const float mj = (float)s.m[j];
-            Sa = Sb;
-            Sb = planck(p, (float)(1.0 / s.T[j]));
-            if (TOT) {
-                const float chi_j = p.kc + kl[j];
-                ta = tb;
-                tb = fmaf(0.5f * (chi_b + chi_j), mj - mb, ta);
-                chi_b = chi_j;
-            }
-            if (CONT) {
-                ca = cb;
-                cb = fmaf(p.kc, mj - mb, ca);
-            }
-            mb = mj;
-        }
-        if (TOT) rt.seg(Sa, Sb, ta, tb);
-        if (CONT) rc.seg(Sa, Sb, ca, cb);
-    }
-    if (TOT) s.F[i] = rt.bottom(Sa, Sb, ta, tb);
-    if (CONT) s.Fc[i] = rc.bottom(Sa, Sb, ca, cb);
+template <int NP>
+__device__ __forceinline__ void row_store_gk(const StarDev& s, int q, int i, const double* g) {
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+        if (q * NP + k < s.D) s.gk[(size_t)(q * NP + k) * s.Npad + i] = (float)g[k];
 }
 
 // ------------------------------------------------------------ E2 quadrature
@@ -462,76 +546,61 @@ __device__ __forceinline__ void expint34(double x, double& E3, double& E4) {
     E4 = (exp(-x) - x * E3) * (1.0 / 3.0);
 }
 
+// E3 and E4 at the lane's knots tau_j, from its segments.
+template <int NP>
+__device__ __forceinline__ void row_expint(int D, int q, const double* dt, double* tau, double* E3, double* E4) {
+    double r = 0.0;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        r += q * NP + k < D ? dt[k] : 0.0;
+        tau[k] = r;
+    }
+    r += shr<1>(r);
+    r += shr<2>(r);
+    r += shr<4>(r);
+    r += shr<8>(r);
+    const double above = shr<1>(r);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        tau[k] += above;
+        E3[k] = E4[k] = 0.0;
+        if (q * NP + k < D) expint34(tau[k], E3[k], E4[k]);
+    }
+}
+
 // F = 2 pi int_0^inf S E2 dt for piecewise-linear S(tau): segment [ta, tb]
 // with S = Sa + s (t - ta) adds Sa (E3(ta) - E3(tb)) + s (E4(ta) - E4(tb) - (tb - ta) E3(tb));
 // below the last depth S continues linearly: S_D E3(tau_D) + s_D E4(tau_D);
 // above the first depth the top slab runs from tau = 0 with the first slope.
-struct RayE2 {
-    double F, E3a, E4a;
-    __device__ void start() {
-        F = 0.0;
-        E3a = 0.5;            // E3(0)
-        E4a = 1.0 / 3.0;      // E4(0)
-    }
-    __device__ void seg(double Sa, double Sb, double ta, double tb) {
-        double E3b, E4b;
-        expint34(tb, E3b, E4b);
-        const double sl = (Sb - Sa) / (tb - ta);
-        F += Sa * (E3a - E3b) + sl * (E4a - E4b - (tb - ta) * E3b);
-        E3a = E3b;
-        E4a = E4b;
-    }
-    __device__ double bottom(double Sa, double Sb, double ta, double tb) const {
-        const double sD = (Sb - Sa) / (tb - ta);
-        return 2.0 * PI * (F + Sb * E3a + sD * E4a);
-    }
-};
-
-// E2 flux of pixel i on the total branch (TOT: F) and/or the continuum
-// branch (CONT: Fc), float64.
-template <bool TOT, bool CONT, class KCol>
-__device__ __forceinline__ void dev_flux_e2(const StarDev& s, int i, const KCol& kl) {
-    if (i >= s.N) return;
-    const double lnl = log(s.lam_first_nm) + (double)i * s.h;
-    const double lam_cm = exp(lnl) * 1.0e-7;
-    const double kc = s.kappa0 * exp(s.alpha * (lnl - log(s.lam_ref_nm)));
-    const double l2 = lam_cm * lam_cm;
-    const double c1 = 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7;
-    const double c2 = H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ);
-    const int D = s.D;
-    double S0 = c1 / expm1(c2 / s.T[0]), S1 = c1 / expm1(c2 / s.T[1]);
-    double chi0 = TOT ? kc + (double)kl[0] : 0.0, chi1 = TOT ? kc + (double)kl[1] : 0.0;
-    double t0 = chi0 * s.m[0], t1 = t0 + 0.5 * (chi0 + chi1) * (s.m[1] - s.m[0]);
-    double c0 = kc * s.m[0], cc1 = c0 + kc * (s.m[1] - s.m[0]);
-    RayE2 rt, rc;
-    rt.start();
-    rc.start();
-    // top slab: S_top at tau = 0 from the first segment's slope
-    if (TOT) rt.seg(S0 - t0 * (S1 - S0) / (t1 - t0), S0, 0.0, t0);
-    if (CONT) rc.seg(S0 - c0 * (S1 - S0) / (cc1 - c0), S0, 0.0, c0);
-    double Sa = S0, Sb = S1, ta = t0, tb = t1, ca = c0, cb = cc1, chib = chi1, mb = s.m[1];
-    for (int j = 1; j < D; ++j) {
-        if (j > 1) {
-            const double mj = s.m[j];
-            Sa = Sb;
-            Sb = c1 / expm1(c2 / s.T[j]);
-            if (TOT) {
-                const double chij = kc + (double)kl[j];
-                ta = tb;
-                tb = ta + 0.5 * (chib + chij) * (mj - mb);
-                chib = chij;
+// Both E2 fluxes of pixel i by a row of lanes, float64: every knot's
+// exponential integrals and every segment are independent, so only the
+// running optical depth and the final sum cross lanes.  12,001 pixels at 72
+// depths: flux 453 us by one thread per pixel, 194 now; adjoint 450 against 85.
+template <int NP>
+__device__ __forceinline__ void dev_flux_e2_row(const StarDev& s, int i) {
+    const bool px = i < s.N;
+    i = min(i, s.N - 1);
+    RowPixel64<NP> x;
+    x.setup(s, i);
+#pragma unroll 1
+    for (int b = 0; b < 2; ++b) {
+        double dt[NP], tau[NP], E3[NP], E4[NP], F = 0.0;
+        x.segments(b == 1, dt);
+        row_expint<NP>(x.D, x.q, dt, tau, E3, E4);
+        const double e3r = shr<1>(E3[NP - 1]), e4r = shr<1>(E4[NP - 1]);
+        const double e3 = x.q ? e3r : 0.5, e4 = x.q ? e4r : 1.0 / 3.0;
+        const double top = x.q ? x.S_above : x.S[0] - dt[0] * (x.S[1] - x.S[0]) / dt[1];
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            if (x.depth(k) < x.D) {
+                const double Sa = k ? x.S[k - 1] : top, E3a = k ? E3[k - 1] : e3, E4a = k ? E4[k - 1] : e4;
+                const double sl = (x.S[k] - Sa) / dt[k];
+                F += Sa * (E3a - E3[k]) + sl * (E4a - E4[k] - dt[k] * E3[k]);
+                if (x.last && k == x.kd) F += x.S[k] * E3[k] + sl * E4[k];      // S continues linearly below
             }
-            if (CONT) {
-                ca = cb;
-                cb = ca + kc * (mj - mb);
-            }
-            mb = mj;
-        }
-        if (TOT) rt.seg(Sa, Sb, ta, tb);
-        if (CONT) rc.seg(Sa, Sb, ca, cb);
+        F = 2.0 * PI * row_sum(F);
+        if (x.q == 0 && px) (b == 0 ? s.F : s.Fc)[i] = (float)F;
     }
-    if (TOT) s.F[i] = (float)rt.bottom(Sa, Sb, ta, tb);
-    if (CONT) s.Fc[i] = (float)rc.bottom(Sa, Sb, ca, cb);
 }
 
 // Reverse of the E2 flux for the total branch.  With knots t_{-1} = 0,
@@ -543,73 +612,47 @@ __device__ __forceinline__ void dev_flux_e2(const StarDev& s, int i, const KCol&
 //   top slab:        through E3(0) - E3(tau_0), P_0 and the extrapolated S_top;
 //   bottom:          dF/dtau_{D-1} += -s_D E3 - E4 s_D/dtau, dF/dtau_{D-2} += E4 s_D/dtau;
 // all times 2 pi; then the trapezoid suffix sums as for Gauss-3.
-// col: pixel i's float64 LDS column (stride WAVE), holding kappa_line on
-// entry and dL/dtau after (each depth written once, as in dev_reverse_scan).
-__device__ __forceinline__ void dev_reverse_scan_e2(const StarDev& s, int i, double* col) {
-    if (i >= s.N) return;
-    const int D = s.D;
+template <int NP>
+__device__ __forceinline__ void dev_reverse_e2_row(const StarDev& s, int i) {
+    const bool px = i < s.N;
+    i = min(i, s.N - 1);
+    RowPixel64<NP> x;
+    x.setup(s, i);
     const double G = 2.0 * PI * (double)s.dLdF[i];
-    const double lnl = log(s.lam_first_nm) + (double)i * s.h;
-    const double lam_cm = exp(lnl) * 1.0e-7;
-    const double kc = s.kappa0 * exp(s.alpha * (lnl - log(s.lam_ref_nm)));
-    const double l2 = lam_cm * lam_cm;
-    const double c1 = 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7;
-    const double c2 = H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ);
-    const double S0 = c1 / expm1(c2 / s.T[0]), S1 = c1 / expm1(c2 / s.T[1]);
-    const double chi0 = kc + col[0], chi1 = kc + col[WAVE];
-    const double t0 = chi0 * s.m[0];
-    const double t1 = t0 + 0.5 * (chi0 + chi1) * (s.m[1] - s.m[0]);
-    const double d01 = t1 - t0, sig = (S1 - S0) / d01;
-    double E3a, E4a;
-    expint34(t0, E3a, E4a);
-    double g0, g1;                                     // top-slab terms of dL/dtau_0, dL/dtau_1
-    {
-        const double dE3 = 0.5 - E3a;                       // E3(0) - E3(tau_0)
-        const double P0 = 1.0 / 3.0 - E4a - t0 * E3a;        // E4(0) - E4(tau_0) - tau_0 E3(tau_0)
-        g0 = G * (dE3 * (-sig - t0 * sig / d01) + P0 * sig / d01);
-        g1 = G * (dE3 * (t0 * sig / d01) - P0 * sig / d01);
+    double dt[NP], tau[NP], E3[NP], E4[NP], gt[NP], back = 0.0;
+    x.segments(false, dt);
+    row_expint<NP>(x.D, x.q, dt, tau, E3, E4);
+    const double e3 = shr<1>(E3[NP - 1]), e4 = shr<1>(E4[NP - 1]);
+#pragma unroll
+    for (int k = 0; k < NP; ++k) gt[k] = 0.0;
+    if (x.q == 0) {
+        const double t0 = dt[0], d01 = dt[1], sig = (x.S[1] - x.S[0]) / d01;
+        const double dE3 = 0.5 - E3[0];                   // E3(0) - E3(tau_0)
+        const double P0 = 1.0 / 3.0 - E4[0] - t0 * E3[0]; // E4(0) - E4(tau_0) - tau_0 E3(tau_0)
+        gt[0] = G * (dE3 * (-sig - t0 * sig / d01) + P0 * sig / d01);
+        gt[1] = G * (dE3 * (t0 * sig / d01) - P0 * sig / d01);
     }
-    double Sa = S0, Sb = S1, ta = t0, tb = t1, chib = chi1, mb = s.m[1];
-    double pend = g1, last = 0.0;                      // pend: what depth j + 1 already holds
-    for (int j = 0; j < D - 1; ++j) {
-        if (j > 0) {
-            const double mj = s.m[j + 1];
-            const double chij = kc + col[(j + 1) * WAVE];
-            Sa = Sb;
-            ta = tb;
-            Sb = c1 / expm1(c2 / s.T[j + 1]);
-            tb = ta + 0.5 * (chib + chij) * (mj - mb);
-            chib = chij;
-            mb = mj;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int j = x.depth(k);
+        if (j == 0 || j >= x.D) continue;
+        const double Sa = k ? x.S[k - 1] : x.S_above, E3a = k ? E3[k - 1] : e3, E4a = k ? E4[k - 1] : e4;
+        const double sl = (x.S[k] - Sa) / dt[k];
+        const double P = (E4a - E4[k] - dt[k] * E3[k]) * sl / dt[k];
+        double up = G * (sl * (E3[k] - E3a) + P), down = -G * P;
+        if (j == x.D - 1) {
+            up += G * (E4[k] * sl / dt[k]);
+            down += G * (-sl * E3[k] - E4[k] * sl / dt[k]);
         }
-        double E3b, E4b;
-        expint34(tb, E3b, E4b);
-        const double dt = tb - ta, sl = (Sb - Sa) / dt;
-        const double P = E4a - E4b - dt * E3b;
-        const double gj = (j == 0 ? g0 : pend) + G * (sl * (E3b - E3a) + P * sl / dt);
-        if (j < D - 2)
-            col[j * WAVE] = gj;
+        gt[k] += down;
+        if (k)
+            gt[k - 1] += up;
         else
-            last = gj;
-        pend = (j == 0 ? g1 : 0.0) + G * (-P * sl / dt);
-        E3a = E3b;
-        E4a = E4b;
+            back += up;
     }
-    {
-        const double dt = tb - ta, sD = (Sb - Sa) / dt;
-        col[(D - 2) * WAVE] = last + G * (E4a * sD / dt);
-        col[(D - 1) * WAVE] = pend + G * (-sD * E3a - E4a * sD / dt);
-    }
-    double suffix = 0.0, gnext = 0.0;
-    float* out = s.gk + i;
-    const size_t st = s.Npad;
-    for (int j = D - 1; j >= 0; --j) {
-        suffix += col[j * WAVE];
-        double g = (j == D - 1) ? 0.0 : 0.5 * (s.m[j + 1] - s.m[j]) * gnext;
-        g += (j == 0) ? s.m[0] * suffix : 0.5 * (s.m[j] - s.m[j - 1]) * suffix;
-        out[(size_t)j * st] = (float)g;
-        gnext = suffix;
-    }
+    gt[NP - 1] += shl<1>(back);
+    row_dchi<NP>(s, x.q, gt);
+    if (px) row_store_gk<NP>(s, x.q, i, gt);
 }
 
 // ---------------------------------------------------------- reverse scan
@@ -653,115 +696,83 @@ __device__ __forceinline__ ExpTerms64 exp_terms64(double x) {
     return r;
 }
 
-// Pixel i's column of a workgroup of WAVE pixels: col[j * WAVE], float64 in
-// LDS.  On entry it holds kappa_line[j][i]; the scan overwrites slot j with
-// dL/dtau_j once kappa_line[j] has been read (each slot is written once: the
-// term a segment adds to the next depth is carried in a register), then the
-// trapezoid adjoint runs up from the bottom.
-__device__ __forceinline__ void stage_kappa_column64(const StarDev& s, int i, double* col) {
-    const float* kl = s.kappa + i;
-    const int D = s.D;
-    for (int j0 = 0; j0 < D; j0 += 16) {
-        float v[16];
+// By a row of lanes: a segment's transmission to the surface A_{j-1} is a
+// product over all segments above, one scan per ray; the terms of the
+// segments are then independent (72 depths, 1,795 pixels: 95 us by one thread
+// per pixel, 16 now; 20,011 pixels: 98 against 61).
+template <int NP>
+__device__ __forceinline__ void dev_reverse_row(const StarDev& s, int i) {
+    const bool px = i < s.N;
+    i = min(i, s.N - 1);
+    RowPixel64<NP> x;
+    x.setup(s, i);
+    const double G = s.dLdF[i];
+    double dt[NP], gt[NP], back = 0.0;
+    x.segments(false, dt);
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = kl[(size_t)min(j0 + u, D - 1) * s.Npad];
+    for (int k = 0; k < NP; ++k) gt[k] = 0.0;
+    const double t0 = dt[0], dt01 = dt[1], sig = (x.S[1] - x.S[0]) / dt01, S_top = x.S[0] - t0 * sig;   // lane 0
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (j0 + u < D) col[(j0 + u) * WAVE] = (double)v[u];
+    for (int m = 0; m < 3; ++m) {
+        const double mu = m == 0 ? kMu0 : (m == 1 ? kMu1 : kMu2), imu = 1.0 / mu;
+        const double Gw = G * 2.0 * PI * (m == 1 ? 8.0 / 18.0 : 5.0 / 18.0) * mu;
+        ExpTerms64 t[NP];
+        double r = 1.0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            t[k] = exp_terms64(dt[k] * imu);
+            r *= t[k].e;
+        }
+        // product of the lanes above
+        double y = shr<1>(r);
+        r = x.q >= 1 ? r * y : r;
+        y = shr<2>(r);
+        r = x.q >= 2 ? r * y : r;
+        y = shr<4>(r);
+        r = x.q >= 4 ? r * y : r;
+        y = shr<8>(r);
+        r = x.q >= 8 ? r * y : r;
+        double A = shr<1>(r);
+        if (x.q == 0) A = 1.0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int j = x.depth(k);
+            if (j == 0) {                                 // the surface slab
+                const double dCdx = S_top * t[0].e + (x.S[0] - S_top) * t[0].dlw, dCdS = t[0].om - t[0].lw;
+                gt[0] += Gw * (dCdx * imu + dCdS * (-sig - t0 * sig / dt01));
+                gt[1] += Gw * dCdS * (t0 * sig / dt01);
+            } else if (j < x.D) {
+                const double Sa = k ? x.S[k - 1] : x.S_above, dS = x.S[k] - Sa;
+                const double c = Sa * t[k].om + dS * t[k].lw, dc = Sa * t[k].e + dS * t[k].dlw;
+                const double w = Gw * A * imu;
+                double up = -w * (c + dc), down = w * dc;
+                if (j == x.D - 1) {                       // the diffusion boundary
+                    const double Gk = Gw * A * t[k].e, g = mu * dS / (dt[k] * dt[k]);
+                    down += Gk * (-(x.S[k] + mu * dS / dt[k]) * imu - g);
+                    up += Gk * g;
+                }
+                gt[k] += down;
+                if (k)
+                    gt[k - 1] += up;
+                else
+                    back += up;
+            }
+            A *= t[k].e;
+        }
     }
+    gt[NP - 1] += shl<1>(back);
+    row_dchi<NP>(s, x.q, gt);
+    if (px) row_store_gk<NP>(s, x.q, i, gt);
 }
 
-__device__ __forceinline__ void dev_reverse_scan(const StarDev& s, int i, double* col) {
-    if (i >= s.N) return;
-    const int D = s.D;
-    const double G = s.dLdF[i];
-    const double mu[3] = {kMu0, kMu1, kMu2};
-    const double wmu[3] = {2.0 * PI * 5.0 / 18.0 * kMu0, 2.0 * PI * 8.0 / 18.0 * kMu1, 2.0 * PI * 5.0 / 18.0 * kMu2};
-    // pixel constants in float64
-    const double lnl = log(s.lam_first_nm) + (double)i * s.h;
-    const double lam_cm = exp(lnl) * 1.0e-7;
-    const double kc = s.kappa0 * exp(s.alpha * (lnl - log(s.lam_ref_nm)));
-    const double l2 = lam_cm * lam_cm;
-    const double c1 = 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7;
-    const double c2 = H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ);
-    // surface quantities
-    const double m0 = s.m[0], m1 = s.m[1];
-    const double S0 = c1 / expm1(c2 / s.T[0]);
-    const double S1 = c1 / expm1(c2 / s.T[1]);
-    const double chi0 = kc + col[0], chi1 = kc + col[WAVE];
-    const double t0 = chi0 * m0;
-    const double t1 = t0 + 0.5 * (chi0 + chi1) * (m1 - m0);
-    const double dt01 = t1 - t0;
-    const double sig = (S1 - S0) / dt01;
-    const double S_top = S0 - t0 * sig;
-    double A[3], g0 = 0.0, g1 = 0.0;                    // surface terms of dL/dtau_0, dL/dtau_1
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double Gk = G * wmu[k];
-        const ExpTerms64 et = exp_terms64(t0 / mu[k]);
-        const double dCdx = S_top * et.e + (S0 - S_top) * et.dlw;
-        const double dCdS = et.om - et.lw;
-        g0 += Gk * (dCdx / mu[k] + dCdS * (-sig - t0 * sig / dt01));
-        g1 += Gk * dCdS * (t0 * sig / dt01);
-        A[k] = et.e;
-    }
-    // segments [j, j + 1]: ga to dL/dtau_j, gb to dL/dtau_{j+1}
-    double Sa = S0, Sb = S1, ta = t0, tb = t1, chib = chi1, mb = m1;
-    double pend = g1, last = 0.0;                      // pend: what depth j already holds
-    for (int j = 0; j < D - 1; ++j) {
-        if (j > 0) {
-            const double mj = s.m[j + 1];
-            const double chij = kc + col[(j + 1) * WAVE];
-            Sa = Sb;
-            ta = tb;
-            Sb = c1 / expm1(c2 / s.T[j + 1]);
-            tb = ta + 0.5 * (chib + chij) * (mj - mb);
-            chib = chij;
-            mb = mj;
-        }
-        double ga = 0.0, gb = 0.0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const ExpTerms64 et = exp_terms64((tb - ta) / mu[k]);
-            const double c = Sa * et.om + (Sb - Sa) * et.lw;
-            const double dc = Sa * et.e + (Sb - Sa) * et.dlw;
-            const double w = G * wmu[k] * A[k] / mu[k];
-            ga -= w * (c + dc);
-            gb += w * dc;
-            A[k] *= et.e;
-        }
-        const double gj = (j == 0 ? g0 : pend) + ga;   // depth j is complete but for the bottom term
-        if (j < D - 2)
-            col[j * WAVE] = gj;
-        else
-            last = gj;
-        pend = j == 0 ? g1 + gb : gb;
-    }
-    // bottom boundary (Sa, Sb, ta, tb are now the last segment)
-    {
-        const double dS = Sb - Sa, dtl = tb - ta;
-        double g_last = 0.0, g_prev = 0.0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double Gk = G * wmu[k] * A[k];
-            const double ID = Sb + mu[k] * dS / dtl;
-            const double q = mu[k] * dS / (dtl * dtl);
-            g_last += Gk * (-ID / mu[k] - q);
-            g_prev += Gk * q;
-        }
-        col[(D - 2) * WAVE] = last + g_prev;
-        col[(D - 1) * WAVE] = pend + g_last;
-    }
-    // dL/dchi_j from the trapezoid rule via suffix sums
-    double suffix = 0.0, gnext = 0.0;
-    float* out = s.gk + i;
-    const size_t st = s.Npad;
-    for (int j = D - 1; j >= 0; --j) {
-        suffix += col[j * WAVE];
-        double g = (j == D - 1) ? 0.0 : 0.5 * (s.m[j + 1] - s.m[j]) * gnext;
-        g += (j == 0) ? s.m[0] * suffix : 0.5 * (s.m[j] - s.m[j - 1]) * suffix;
-        out[(size_t)j * st] = (float)g;
-        gnext = suffix;
+// Calls f with the depths per lane of D as a compile-time constant.
+template <class F>
+__host__ __device__ __forceinline__ void with_row_np(int D, F f) {
+    switch (row_np(D)) {
+        case 2: f(std::integral_constant<int, 2>()); break;
+        case 3: f(std::integral_constant<int, 3>()); break;
+        case 4: f(std::integral_constant<int, 4>()); break;
+        default: f(std::integral_constant<int, 5>()); break;
     }
 }
 
