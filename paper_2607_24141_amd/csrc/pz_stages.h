@@ -8,6 +8,7 @@
 
 #include <type_traits>
 
+#include "expint_consts.h"
 #include "pz_internal.h"
 #include "pz_rows.h"
 #include "pz_voigt.h"
@@ -485,52 +486,16 @@ __device__ __forceinline__ void row_store_gk(const StarDev& s, int q, int i, con
 }
 
 // ------------------------------------------------------------ E2 quadrature
-// Exponential integrals E_n(x), n = 2..4, x >= 0, in float64:
-//   x <= 1: power series E_n(x) = (-x)^{n-1}/(n-1)! (psi(n) - ln x)
-//                                 - sum_{k != n-1} (-x)^k / ((k - n + 1) k!),
-//           psi(n) = -gamma + sum_{m<n} 1/m;
-//   x > 1:  continued fraction E_n(x) = e^{-x} / (x + n - 1 n/(x + n + 2 - 2 (n+1)/(x + n + 4 - ...)))
-//           evaluated with the modified Lentz method.
-// Both loops have fixed upper bounds.
-__device__ __forceinline__ double expint_n(int n, double x) {
-    if (x <= 0.0) return 1.0 / (n - 1);
-    if (x > 700.0) return 0.0;
-    if (x <= 1.0) {
-        const double euler = 0.57721566490153286061;
-        double psi = -euler;
-        for (int m = 1; m < n; ++m) psi += 1.0 / m;
-        double term = 1.0;                       // (-x)^k / k!
-        double sum = (n == 1) ? 0.0 : -1.0 / (1.0 - n);   // k = 0
-        double lead = 0.0;
-        for (int k = 1; k < 60; ++k) {
-            term *= -x / k;
-            if (k == n - 1) {
-                lead = term * (psi - log(x));
-            } else {
-                const double t = term / (k - n + 1);
-                sum -= t;
-                if (k > n && fabs(t) < 1e-18 * fabs(sum)) break;
-            }
-        }
-        return lead + sum;
-    }
-    const double tiny = 1e-300;
-    double b = x + n, c = 1.0 / tiny, d = 1.0 / b, h = d;
-    for (int i = 1; i < 400; ++i) {
-        const double an = -(double)i * (n - 1 + i);
-        b += 2.0;
-        d = 1.0 / (an * d + b);
-        c = b + an / c;
-        const double del = c * d;
-        h *= del;
-        if (fabs(del - 1.0) < 1e-16) break;
-    }
-    return h * exp(-x);
-}
-
-// E3(x) and E4(x) = (e^-x - x E3(x)) / 3 (the recurrence E_{n+1} = (e^-x -
-// x E_n) / n; its cancellation for large x costs at most ~3 of float64's 16
-// digits below x = 700, beyond which both are 0).
+// E3(x) and E4(x) = (e^-x - x E3(x)) / 3 for x >= 0, float64 (the recurrence
+// E_{n+1} = (e^-x - x E_n) / n; its cancellation for large x costs at most ~3
+// of float64's 16 digits below x = 700, beyond which both are 0).  E3 is its
+// power series up to x = 1 and e^-x / x times a polynomial in 1/x per octave
+// beyond (expint_consts.h), to 7e-15 relative, as a series and a continued
+// fraction summed to their ends are.  Those ends lie up to ninety divisions
+// away near x = 1, and a wavefront waits for its slowest knot: 194 against 24 us
+// for the flux, 85 against 17 for the adjoint (12,001 pixels, 72 depths).
+__constant__ double c_e3_series[PZ_E3_SERIES_N] = {PZ_E3_SERIES};
+__constant__ double c_e3_table[PZ_E3_OCTAVES * (PZ_E3_DEGREE + 1)] = {PZ_E3_TABLE};
 __device__ __forceinline__ void expint34(double x, double& E3, double& E4) {
     if (x <= 0.0) {
         E3 = 0.5;
@@ -542,8 +507,24 @@ __device__ __forceinline__ void expint34(double x, double& E3, double& E4) {
         E4 = 0.0;
         return;
     }
-    E3 = expint_n(3, x);
-    E4 = (exp(-x) - x * E3) * (1.0 / 3.0);
+    const double e = exp(-x);
+    if (x <= 1.0) {
+        double p = 0.0;
+#pragma unroll
+        for (int k = PZ_E3_SERIES_N - 1; k >= 0; --k) p = fma(p, x, c_e3_series[k]);
+        E3 = 0.5 - x + x * x * fma(x, p, 0.5 * (PZ_E3_PSI - log(x)));
+    } else {
+        const double y = 1.0 / x;
+        const int o = min(ilogb(x), PZ_E3_OCTAVES - 1);    // [2^o, 2^{o+1}); the last one open
+        const double hi = ldexp(1.0, -o), lo = o == PZ_E3_OCTAVES - 1 ? 0.0 : 0.5 * hi;
+        const double t = (y - lo) * (2.0 / (hi - lo)) - 1.0;
+        const double* c = c_e3_table + max(o, 0) * (PZ_E3_DEGREE + 1);   // a NaN indexes row 0 and stays one
+        double p = 0.0;
+#pragma unroll
+        for (int k = PZ_E3_DEGREE; k >= 0; --k) p = fma(p, t, c[k]);
+        E3 = e * y * p;
+    }
+    E4 = (e - x * E3) * (1.0 / 3.0);
 }
 
 // E3 and E4 at the lane's knots tau_j, from its segments.
@@ -575,7 +556,8 @@ __device__ __forceinline__ void row_expint(int D, int q, const double* dt, doubl
 // Both E2 fluxes of pixel i by a row of lanes, float64: every knot's
 // exponential integrals and every segment are independent, so only the
 // running optical depth and the final sum cross lanes.  12,001 pixels at 72
-// depths: flux 453 us by one thread per pixel, 194 now; adjoint 450 against 85.
+// depths: flux 453 us by one thread per pixel, 24 now; adjoint 450 against 17 (194 and
+// 85 before the exponential integrals below were made polynomials).
 template <int NP>
 __device__ __forceinline__ void dev_flux_e2_row(const StarDev& s, int i) {
     const bool px = i < s.N;
