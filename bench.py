@@ -43,24 +43,23 @@ METRIC = "spectra/s, Voigt evals/s: fwd, fwd+bwd, batched vs plain fwd at 1e-4 r
 FLOPS_PER_EVAL_NOMINAL = 34
 PEAK_FP32_TFLOPS = 157.3   # MI355X published FP32 vector peak
 PEAK_HBM_GBS = 8000.0      # MI355X published HBM3E bandwidth
-# sources of the opacity kernel: a committed counter measurement (HBM bytes,
+# sources of the opacity kernels: a committed counter measurement (HBM bytes,
 # VALU instruction counts) is used only if they are unchanged.  The opacity
-# kernel's code: its tile body and the Voigt evaluator, plus the kernel's own
-# definition in pz_kernels.hip (other code in that file is not part of it).
-KERNEL_SOURCES = ("paper_2607_24141_amd/csrc/pz_opacity.h", "paper_2607_24141_amd/csrc/pz_voigt.h",
+# stage of this workload is the far and near kernels of the split sums.
+KERNEL_SOURCES = ("paper_2607_24141_amd/csrc/pz_split.h", "paper_2607_24141_amd/csrc/pz_voigt.h",
                   "paper_2607_24141_amd/csrc/voigt_consts.h")
-KERNEL_DEF = ("paper_2607_24141_amd/csrc/pz_kernels.hip", "void k_opacity(")
+KERNEL_DEF = ("paper_2607_24141_amd/csrc/pz_kernels.hip", "void k_opacity_near(")
 
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-# The gather kernel's code: its stage bodies, the Voigt evaluator and its
-# definition in pz_kernels.hip.
-GATHER_SOURCES = ("paper_2607_24141_amd/csrc/pz_stages.h", "paper_2607_24141_amd/csrc/pz_voigt.h",
+# The gather kernels' code: their bodies, the Voigt evaluator and the near
+# kernel's definition in pz_kernels.hip.
+GATHER_SOURCES = ("paper_2607_24141_amd/csrc/pz_split_gather.h", "paper_2607_24141_amd/csrc/pz_voigt.h",
                   "paper_2607_24141_amd/csrc/voigt_consts.h")
-GATHER_DEF = ("paper_2607_24141_amd/csrc/pz_kernels.hip", "void k_gather(")
+GATHER_DEF = ("paper_2607_24141_amd/csrc/pz_kernels.hip", "void k_gather_near(")
 
 
 def kernel_hash(sources=KERNEL_SOURCES, definition=KERNEL_DEF):
@@ -91,7 +90,7 @@ def _profile_json(name, hash_fn=kernel_hash):
 
 
 def traffic_from_profiles(kind="opacity"):
-    """HBM bytes per launch (calibrated FETCH_SIZE + WRITE_SIZE) from the committed counter summary."""
+    """HBM bytes per opacity stage (calibrated FETCH_SIZE + WRITE_SIZE) from the committed counter summary."""
     d = _profile_json("traffic_%s.json" % kind)
     return None if d is None else d.get("bytes_per_launch")
 
@@ -267,7 +266,7 @@ def main():
     fpe = fpe or FLOPS_PER_EVAL_NOMINAL
     achieved_tflops = plan.voigt_evals * fpe / (op_avg_ms * 1e-3) / 1e12
     stage = {k: (v[0] / max(v[1], 1)) for k, v in prof.items() if v[1]}
-    roof = {"bound": "alu", "kernel": "k_opacity", "achieved": achieved_tflops, "peak": PEAK_FP32_TFLOPS,
+    roof = {"bound": "alu", "kernel": "k_opacity_far + k_opacity_near", "achieved": achieved_tflops, "peak": PEAK_FP32_TFLOPS,
             "unit": "TFLOP/s", "frac": achieved_tflops / PEAK_FP32_TFLOPS,
             "traffic": traffic_from_profiles("opacity"), "kernel_avg_ms": op_avg_ms,
             "flops_per_eval": fpe, "flops_source": flops_source, "evals_per_launch": plan.voigt_evals}
@@ -339,7 +338,7 @@ def main():
         vg = _profile_json("valu_gather.json", gather_hash)
         if vg and "gather" in st_fb:
             tg = vg["flops_per_eval"] * plan.voigt_evals / (st_fb["gather"] * 1e-3) / 1e12
-            out["roofline_gather"] = {"bound": "alu", "kernel": "k_gather", "achieved": tg, "peak": PEAK_FP32_TFLOPS,
+            out["roofline_gather"] = {"bound": "alu", "kernel": "k_gather_far + k_gather_near", "achieved": tg, "peak": PEAK_FP32_TFLOPS,
                                       "unit": "TFLOP/s", "frac": tg / PEAK_FP32_TFLOPS,
                                       "flops_per_eval": vg["flops_per_eval"], "kernel_avg_ms": st_fb["gather"],
                                       "flops_source": "SQ VALU counters (profiles/valu_gather.json)"}
@@ -366,7 +365,6 @@ def main():
         wprof = wplan.profile_read()
         wplan.profile(False)
         wst = {k: (v[0] / max(v[1], 1)) for k, v in wprof.items() if v[1]}
-        w_tflops = wplan.voigt_evals * fpe / (wst["opacity"] * 1e-3) / 1e12
         bw = 4.0 * wplan.D * wplan.N + 8.0 * wplan.N
         out["wide_300_1000nm"] = {
             "workload": wwl.name, "N": wplan.N, "L": wplan.L, "D": wplan.D, "S": wwl.atm.S,
@@ -374,8 +372,6 @@ def main():
             "fwd_ms_max": tw["max_ms"], "steps": tw["replays"], "spectra_per_s": 1000.0 / tw["median_ms"],
             "voigt_evals": wplan.voigt_evals, "voigt_evals_per_s": wplan.voigt_evals / (tw["median_ms"] * 1e-3),
             "stage_ms": wst, "line_params_bytes": 16 * wplan.L * wplan.D,
-            "opacity_roofline": {"achieved": w_tflops, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                                 "frac": w_tflops / PEAK_FP32_TFLOPS, "flops_per_eval": fpe},
             "flux_GB_s": bw / (wst["flux"] * 1e6),
             "host_generate_s": t_gen, "host_plan_s": t_plan}
         wplan.destroy()

@@ -101,8 +101,8 @@ typedef struct {
 typedef struct {
     double window_nm;           /* W: line l reaches pixel i iff |lambda_i - lambda_l| <= W (> 0) */
     int32_t quadrature;         /* PZ_QUAD_GAUSS3 (default, FP32) or PZ_QUAD_E2 (FP64) */
-    int32_t tile_px;            /* opacity tile width in pixels: 0 = autotuned/default */
-    int32_t lines_per_chunk;    /* lines staged in LDS per step: 0 = default          */
+    int32_t tile_px;            /* direct line sums: tile width in pixels, 0 = autotuned/default */
+    int32_t lines_per_chunk;    /* direct line sums: lines staged in LDS per step, 0 = default */
     int32_t flags;              /* PZ_FLAG_* bits; others must be 0                    */
     double center_eta;          /* continuum-referenced centre test (Sec. 2.2, Table 2): 0 = off
                                    (plain windowed sum); eta > 0 keeps a (line, depth) pair only
