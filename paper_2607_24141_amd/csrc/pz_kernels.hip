@@ -29,8 +29,10 @@ __global__ __launch_bounds__(256) void k_line_params(StarDev s) {
 // tail of heavy tiles.
 // CT: the plan uses the centre test (its LDS holds the zmax rows); G: depth-group
 // slots per lane (at least D / (64 / WPX)); FG: exactly D / (64 / WPX).
-template <int WPX, bool CT, int G, bool FG>
-__global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void k_opacity(StarDev s, int chunk) {
+// NTH: threads per workgroup, 512 for a whole tile or a part of it.
+template <int WPX, bool CT, int G, bool FG, int NTH>
+__global__ __launch_bounds__(NTH) PZ_OPACITY_WAVES(WPX) void k_opacity(StarDev s, int chunk) {
+    constexpr int PARTS = 512 / NTH;
     PZ_OPACITY_LDS(WPX, CT, sm);
     __shared__ int s_it;
     load_pw_table(sm.pw, false);                       // visible after the first item fetch's barrier
@@ -39,8 +41,8 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void k_opacity(StarDev s
         __syncthreads();
         const int it = __builtin_amdgcn_readfirstlane(s_it);
         __syncthreads();
-        if (it >= s.n_tiles) return;
-        dev_opacity_tile<WPX, false, CT, G, true, FG>(s, s.tile_order[it], 0, chunk, sm);
+        if (it >= s.n_tiles * PARTS) return;
+        dev_opacity_tile<WPX, false, CT, G, true, FG, NTH>(s, s.tile_order[it / PARTS], it % PARTS, chunk, sm);
     }
 }
 
@@ -84,9 +86,9 @@ __global__ __launch_bounds__(256) void k_select(StarDev s, double eta, double bi
 template <bool CT>
 static hipError_t opacity_occupancy(int tile_px, int* occ) {
     switch (tile_px) {
-        case 32: return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, k_opacity<4, CT, 4, true>, 512, 0);
-        case 64: return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, k_opacity<8, CT, 9, true>, 512, 0);
-        default: return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, k_opacity<16, CT, 19, false>, 512, 0);
+        case 32: return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, k_opacity<4, CT, 4, true, 512>, 512, 0);
+        case 64: return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, k_opacity<8, CT, 9, true, 512>, 512, 0);
+        default: return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, k_opacity<16, CT, 19, false, 512>, 512, 0);
     }
 }
 
@@ -310,16 +312,32 @@ hipError_t launch_line_params(const StarDev& s, hipStream_t st) {
 
 // The main pass with the fewest depth-group slots that hold D / (64 / WPX)
 // groups (with no empty slot where the depths allow), then the wide pass.
-template <int WPX, bool CT>
-static void launch_opacity_wpx(const StarDev& s, int chunk, int grid, hipStream_t st) {
+template <int WPX, bool CT, int NTH>
+static void launch_opacity_parts(const StarDev& s, int chunk, hipStream_t st) {
     constexpr int GB = opacity_max_groups<WPX>();
     const int ng = s.D / (64 / WPX);                   // <= GB: D <= MAXD
+    const int grid = std::max(1, std::min(s.grid_opacity, s.n_tiles * (512 / NTH)));
     if (ng == GB)
-        k_opacity<WPX, CT, GB, true><<<grid, 512, 0, st>>>(s, chunk);
+        k_opacity<WPX, CT, GB, true, NTH><<<grid, NTH, 0, st>>>(s, chunk);
     else if (ng == GB - 1)
-        k_opacity<WPX, CT, GB - 1, true><<<grid, 512, 0, st>>>(s, chunk);
+        k_opacity<WPX, CT, GB - 1, true, NTH><<<grid, NTH, 0, st>>>(s, chunk);
     else
-        k_opacity<WPX, CT, GB - 1, false><<<grid, 512, 0, st>>>(s, chunk);
+        k_opacity<WPX, CT, GB - 1, false, NTH><<<grid, NTH, 0, st>>>(s, chunk);
+}
+
+// With fewer tiles than the chip holds, a tile goes to two workgroups of half
+// its wavefronts each, which stage the lines for themselves: the sums and their
+// order stay the same.  64-pixel tiles, forward calls at 72 depths, whole
+// against halves: 16 tiles 815 and 711 us, 69 949 and 835, 124 980 and 851, 188
+// 1506 and 1264, 313 1646 and 1300; 579 (more than the 512 the chip holds)
+// 2021 and 2121.  Quarters gain nothing more, and 32-pixel tiles (137: 543 and
+// 555 us) nothing at all.
+template <int WPX, bool CT>
+static void launch_opacity_wpx(const StarDev& s, int chunk, int grid, hipStream_t st) {
+    if (WPX > 4 && 3 * s.n_tiles <= 2 * s.grid_opacity)
+        launch_opacity_parts<WPX, CT, WPX == 4 ? 512 : 256>(s, chunk, st);
+    else
+        launch_opacity_parts<WPX, CT, 512>(s, chunk, st);
     k_opacity_wide<WPX, CT><<<grid, 512, 0, st>>>(s, chunk);
 }
 
