@@ -557,7 +557,7 @@ __device__ __forceinline__ void row_expint(int D, int q, const double* dt, doubl
 // exponential integrals and every segment are independent, so only the
 // running optical depth and the final sum cross lanes.  12,001 pixels at 72
 // depths: flux 453 us by one thread per pixel, 24 now; adjoint 450 against 17 (194 and
-// 85 before the exponential integrals below were made polynomials).
+// 85 before the exponential integrals above were made polynomials).
 template <int NP>
 __device__ __forceinline__ void dev_flux_e2_row(const StarDev& s, int i) {
     const bool px = i < s.N;
