@@ -40,7 +40,7 @@ enum Phase {
     PH_ROWS,       // (star, ROW_ITEM pixels): transfer, one list for each row_list()
     PH_ROWS_END = PH_ROWS + 7,
     PH_GATHER,     // (star, GATHER_ITEM lines), atomic queue
-    PH_GSPLIT,     // (star, GATHER_ITEM lines) of stars with split sums
+    PH_GSPLIT,     // (star, GATHER_ITEM lines) of stars with split sums, atomic queue
     PH_SCATTER,    // (star, 512 lines)
     PH_PARTIAL,    // (star, list b * n_rchunk + c)
     PH_FINAL,      // (star, list b)
@@ -48,7 +48,7 @@ enum Phase {
 };
 
 constexpr int PARAM_ITEM = 512 * 32;
-constexpr int N_COUNTER = 4;             // queues: opacity x 3 tile widths, gather
+constexpr int N_COUNTER = 5;             // queues: opacity x 3 tile widths, gather, split gather
 constexpr int GATHER_ITEM = 64;
 constexpr int ROW_ITEM = 64;             // pixels of a transfer item: four passes of 16
 int row_list(const pz::StarDev& s) { return PH_ROWS + 2 * (pz::row_np(s.D) - 2) + (s.quad == PZ_QUAD_E2); }
@@ -210,6 +210,8 @@ __global__ __launch_bounds__(1024) void kb_loss(const StarDev* __restrict__ star
     }
 }
 
+// NEAR: the near zone of the split sums, after kb_gather_far.
+template <bool NEAR>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void kb_gather(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n, int* ctr) {
     __shared__ int s_it;
     __shared__ float4 pw[2 * PZ_PW_LDS];
@@ -230,12 +232,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            dev_gather(s, l, lane, pw, lq[wave]);
+            dev_gather<NEAR>(s, l, lane, pw, lq[wave]);
         }
     }
 }
 
-// Split sums: GATHER_ITEM lines per workgroup, by two pairs of wavefronts and then one wavefront per line.
+// Split sums: GATHER_ITEM lines per workgroup, by two pairs of wavefronts.
 __global__ __launch_bounds__(256) void kb_gather_far(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
     const int2 w = uniform_item(items, blockIdx.x);
     const StarDev& s = stars[w.x];
@@ -249,18 +251,6 @@ __global__ __launch_bounds__(256) void kb_gather_far(const StarDev* __restrict__
             dev_gather_far<false>(s, base, wave % 2, hand[wave / 2]);
         __syncthreads();
     }
-}
-
-__global__ __launch_bounds__(256) void kb_gather_near(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
-    __shared__ float4 near_tab[PZ_NEAR_N];
-    __shared__ float4 pw[2 * PZ_PW_LDS];
-    load_near_table(near_tab);
-    load_pw_table(pw, true);
-    __syncthreads();
-    const int2 w = uniform_item(items, blockIdx.x);
-    const StarDev& s = stars[w.x];
-    for (int q = threadIdx.x / WAVE; q < GATHER_ITEM; q += 4)
-        dev_gather_split(s, __builtin_amdgcn_readfirstlane(w.y * GATHER_ITEM + q), threadIdx.x % WAVE, near_tab, pw);
 }
 
 __global__ __launch_bounds__(512) void kb_scatter(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n) {
@@ -316,7 +306,7 @@ struct pz_batch {
     float* inv_s2;
     const float** ys;
     float** losses;
-    int* ctr;             // [N_COUNTER] queue counters: opacity (32, 64, 128), gather
+    int* ctr;             // [N_COUNTER] queue counters: opacity (32, 64, 128), gather, split gather
     int grid512, grid256, grid1024, grid_op[3], grid_gather;
     void* base;
 };
@@ -498,7 +488,7 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
     }
     if (e == hipSuccess)
         e = bt->any_center ? batch_opacity_occupancy<true>(occ_op) : batch_opacity_occupancy<false>(occ_op);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_g, kb_gather, 512, 0);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_g, kb_gather<false>, 512, 0);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         (void)hipFree(base);
@@ -563,11 +553,12 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
         }
         if (n[PH_GSPLIT]) {
             kb_gather_far<<<n[PH_GSPLIT], 256, 0, st>>>(bt->stars, it[PH_GSPLIT]);
-            kb_gather_near<<<n[PH_GSPLIT], 256, 0, st>>>(bt->stars, it[PH_GSPLIT]);
+            kb_gather<true><<<grid(bt->grid_gather, n[PH_GSPLIT]), 512, 0, st>>>(bt->stars, it[PH_GSPLIT], n[PH_GSPLIT],
+                                                                                  bt->ctr + 4);
         }
         if (n[PH_GATHER])
-            kb_gather<<<grid(bt->grid_gather, n[PH_GATHER]), 512, 0, st>>>(bt->stars, it[PH_GATHER], n[PH_GATHER],
-                                                                            bt->ctr + 3);
+            kb_gather<false><<<grid(bt->grid_gather, n[PH_GATHER]), 512, 0, st>>>(bt->stars, it[PH_GATHER], n[PH_GATHER],
+                                                                                   bt->ctr + 3);
         kb_scatter<<<grid(bt->grid512, n[PH_SCATTER]), 512, 0, st>>>(bt->stars, it[PH_SCATTER], n[PH_SCATTER]);
         kb_partial<<<grid(bt->grid256, n[PH_PARTIAL]), 256, 0, st>>>(bt->stars, it[PH_PARTIAL], n[PH_PARTIAL]);
         kb_final<<<grid(bt->grid256, n[PH_FINAL]), 256, 0, st>>>(bt->stars, it[PH_FINAL], n[PH_FINAL]);

@@ -233,6 +233,8 @@ __device__ __forceinline__ int xcd_contiguous_block(int b, int nb) {
     return x * q + min(x, r) + p;
 }
 
+// NEAR: the near zone of the split sums, after k_gather_far.
+template <bool NEAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_gather(StarDev s) {
     __shared__ float4 pw[2 * PZ_PW_LDS];
     __shared__ float4 lq[256 / WAVE][2 * MAXD];
@@ -242,27 +244,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     const int l = __builtin_amdgcn_readfirstlane(blk * (256 / WAVE) + w);
     stage_line_params(s, l, threadIdx.x % WAVE, lq[w]);
     __syncthreads();
-    dev_gather(s, l, threadIdx.x % WAVE, pw, lq[w]);
+    dev_gather<NEAR>(s, l, threadIdx.x % WAVE, pw, lq[w]);
 }
 
-// Split sums: two pairs of wavefronts with 16 lines each, then one wavefront per line.
+// Split sums: two pairs of wavefronts with 16 lines each.
 template <bool FAM>
 __global__ __launch_bounds__(256) void k_gather_far(StarDev s) {
     __shared__ LineSums hand[2][GFAR_LINES];
     const int blk = xcd_contiguous_block(blockIdx.x, gridDim.x), wave = threadIdx.x / WAVE;
     dev_gather_far<FAM>(s, (blk * 2 + wave / 2) * GFAR_LINES, wave % 2, hand[wave / 2]);
-}
-
-template <bool CT, bool FAM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_gather_near(StarDev s) {
-    __shared__ float4 near_tab[PZ_NEAR_N];
-    __shared__ float4 pw[2 * PZ_PW_LDS];
-    load_near_table(near_tab);
-    load_pw_table(pw, true);
-    __syncthreads();
-    const int blk = xcd_contiguous_block(blockIdx.x, gridDim.x);
-    const int l = __builtin_amdgcn_readfirstlane(blk * (256 / WAVE) + threadIdx.x / WAVE);
-    if (l < s.L) dev_gather_near<CT, FAM>(s, l, threadIdx.x % WAVE, near_tab, pw);
 }
 
 __global__ __launch_bounds__(256) void k_scatter_lines(StarDev s) { dev_scatter(s, blockIdx.x * blockDim.x + threadIdx.x); }
@@ -397,18 +387,14 @@ hipError_t launch_reverse_scan(const StarDev& s, hipStream_t st) {
 
 hipError_t launch_gather(const StarDev& s, hipStream_t st) {
     if (s.L == 0) return hipSuccess;
+    const int n = (s.L + 3) / 4;
     if (s.split_gather) {
-        const int far = (s.L + 2 * GFAR_LINES - 1) / (2 * GFAR_LINES), near = (s.L + 3) / 4;
-        if (s.fam) {
-            k_gather_far<true><<<far, 256, 0, st>>>(s);
-            s.center ? k_gather_near<true, true><<<near, 256, 0, st>>>(s) : k_gather_near<false, true><<<near, 256, 0, st>>>(s);
-        } else {
-            k_gather_far<false><<<far, 256, 0, st>>>(s);
-            s.center ? k_gather_near<true, false><<<near, 256, 0, st>>>(s) : k_gather_near<false, false><<<near, 256, 0, st>>>(s);
-        }
-        return hipGetLastError();
+        const int far = (s.L + 2 * GFAR_LINES - 1) / (2 * GFAR_LINES);
+        s.fam ? k_gather_far<true><<<far, 256, 0, st>>>(s) : k_gather_far<false><<<far, 256, 0, st>>>(s);
+        k_gather<true><<<n, 256, 0, st>>>(s);
+    } else {
+        k_gather<false><<<n, 256, 0, st>>>(s);
     }
-    k_gather<<<(s.L + 3) / 4, 256, 0, st>>>(s);
     return hipGetLastError();
 }
 

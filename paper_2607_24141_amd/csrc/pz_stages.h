@@ -809,7 +809,8 @@ __device__ __forceinline__ void far_series(float b, float z2, float& r, float& p
 // series, other steps voigt_KHD.
 // FAM: the damping term is split over the three families by their share of
 // the width at each depth, w_beta = Gamma_beta / Gamma.
-template <bool CT, bool FAM>
+// NEAR: the near zone only; the far zone's sums are in gline (dev_gather_far).
+template <bool CT, bool FAM, bool NEAR>
 __device__ __forceinline__ void gather_body(const StarDev& s, int l, int lane, const float4* pw, const float4* lq) {
     constexpr int WPX = 8, NDG = 8, DPT = (MAXD + NDG - 1) / NDG;
     const int px = lane % WPX, dg = lane / WPX;
@@ -831,11 +832,20 @@ __device__ __forceinline__ void gather_body(const StarDev& s, int l, int lane, c
             ihi = min(ihi, ic + (int)ceil((dl - log1p(-xl)) / h) + 1);
         }
     }
+    const float reach = NEAR ? near_reach(s.xfar[l]) : INFINITY;
+    if (NEAR) {
+        // pixels with |x| < reach lie within (reach + reach^2) / h + 1/2 of the anchor
+        const float w = fmaf(reach, reach, reach) / s.h_hi + 2.0f;
+        if (reach < 0.5f && w < 1.0e6f) {
+            ilo = max(ilo, ic - (int)w);
+            ihi = min(ihi, ic + (int)w);
+        }
+    }
     float sgf = 0.0f, sd = 0.0f, sxi = 0.0f, sds = 0.0f, sdw = 0.0f;
     for (int p0 = ilo; p0 <= ihi; p0 += WPX) {
         const int i = p0 + px;
-        if (i <= ihi) {
-            const float x = detuning(i - ic, delta, s.h_hi, s.h_lo);
+        const float x = detuning(i - ic, delta, s.h_hi, s.h_lo);
+        if (i <= ihi && (!NEAR || fabsf(x) < reach)) {
             const float* g = s.gk + i;
 #pragma unroll 1
             for (int d = 0; d < DPT; ++d) {
@@ -881,6 +891,15 @@ __device__ __forceinline__ void gather_body(const StarDev& s, int l, int lane, c
         sdw = wave_sum(sdw);
     }
     if (lane == 0) {
+        if (NEAR) {
+            sgf += s.gline[l];
+            sd += s.gline[s.L + l];
+            sxi += s.gline[2 * s.L + l];
+            if (FAM) {
+                sds += s.gline[3 * s.L + l];
+                sdw += s.gline[4 * s.L + l];
+            }
+        }
         s.gline[l] = (float)LN10 * sgf;
         s.gline[s.L + l] = (float)LN10 * sd;
         s.gline[2 * s.L + l] = sxi;
@@ -891,18 +910,19 @@ __device__ __forceinline__ void gather_body(const StarDev& s, int l, int lane, c
     }
 }
 
+template <bool NEAR>
 __device__ __forceinline__ void dev_gather(const StarDev& s, int l, int lane, const float4* pw, const float4* lq) {
     if (l >= s.L) return;
     if (s.fam) {
         if (s.center)
-            gather_body<true, true>(s, l, lane, pw, lq);
+            gather_body<true, true, NEAR>(s, l, lane, pw, lq);
         else
-            gather_body<false, true>(s, l, lane, pw, lq);
+            gather_body<false, true, NEAR>(s, l, lane, pw, lq);
     } else {
         if (s.center)
-            gather_body<true, false>(s, l, lane, pw, lq);
+            gather_body<true, false, NEAR>(s, l, lane, pw, lq);
         else
-            gather_body<false, false>(s, l, lane, pw, lq);
+            gather_body<false, false, NEAR>(s, l, lane, pw, lq);
     }
 }
 

@@ -250,40 +250,6 @@ __device__ __forceinline__ float near_KH_acc(float acc, float a2, float K, float
     return fmaf(Ka, lam, fmaf(K * __expf(a2 - u), cs, acc));
 }
 
-// K H, K a dH/da and K X, X = H + a dH/da + v dH/dv, on the near zone: the
-// derivatives of the formula above (v g' = s + g (1 - 2u)), with P = K
-// exp(a^2-u) cos(2av) and Q = 2av K exp(a^2-u) sin(2av):
-//   K a dH/da = 2a^2 P - Q + K a [g + 3 a^2 (..) + 5 a^4 (..)],
-//   K X = (1 + 2(a^2 - u)) P - 2Q + K a [s + g (3 - 2u)
-//         + a^2 (s (7/3 - 2u/3) + g (5 - 20u/3 + 4u^2/3))
-//         + a^4 (s (19/10 - 6u/5 + 2u^2/15) + g (7/2 - 7u + 14u^2/5 - 4u^3/15))].
-template <bool FULL>
-__device__ __forceinline__ void near_KHD(float a2, float K, float Ka, float v, const float4* tab, float& KH,
-                                         float& KaHa, float& KX) {
-    const float u = v * v;
-    const float g = near_g(v, tab);
-    float d1 = fmaf(g, fmaf(-2.0f / 3.0f, u, 1.0f), kNearS / 3.0f), da = 3.0f * d1;
-    float dx = fmaf(g, fmaf(fmaf(4.0f / 3.0f, u, -20.0f / 3.0f), u, 5.0f),
-                    fmaf(-kNearS * 2.0f / 3.0f, u, kNearS * 7.0f / 3.0f));
-    if (FULL) {
-        const float p = fmaf(fmaf(2.0f / 15.0f, u, -2.0f / 3.0f), u, 0.5f);
-        const float h5 = fmaf(g, p, fmaf(-kNearS / 15.0f, u, kNearS * 7.0f / 30.0f));
-        const float q = fmaf(fmaf(fmaf(-4.0f / 15.0f, u, 2.8f), u, -7.0f), u, 3.5f);
-        const float x5 = fmaf(g, q, fmaf(fmaf(kNearS * 2.0f / 15.0f, u, -kNearS * 1.2f), u, kNearS * 1.9f));
-        d1 = fmaf(a2, h5, d1);
-        da = fmaf(5.0f * a2, h5, da);
-        dx = fmaf(a2, x5, dx);
-    }
-    const float y = a2 * u;                             // (2av)^2 / 4
-    const float cs = fmaf(fmaf(fmaf(fmaf(2.0f / 315.0f, y, -4.0f / 45.0f), y, 2.0f / 3.0f), y, -2.0f), y, 1.0f);
-    const float sn = fmaf(fmaf(fmaf(fmaf(2.0f / 2835.0f, y, -4.0f / 315.0f), y, 2.0f / 15.0f), y, -2.0f / 3.0f), y, 1.0f);
-    const float KE = K * __expf(a2 - u);
-    const float P = KE * cs, Q = (4.0f * y) * (KE * sn);
-    KH = fmaf(Ka, fmaf(a2, d1, g), P);
-    KaHa = fmaf(Ka, fmaf(a2, da, g), fmaf(a2 + a2, P, -Q));
-    KX = fmaf(Ka, fmaf(a2, dx, fmaf(g, fmaf(-2.0f, u, 3.0f), kNearS)), fmaf(fmaf(2.0f, a2 - u, 1.0f), P, -2.0f * Q));
-}
-
 // Far zone, v >= PZ_FAR_V and a <= PZ_FAR_AV v at every depth of a line: with
 // x0 the line's zone limit and U = (x0/x)^2, w = 1/v^2 = W U, W = 1/(s x0)^2,
 //   K H = sum_n C_n U^n,  C_n = (K a/sqrt(pi)) W^n P_(n-1)(a^2),  n = 1..PZ_FAR_N:
