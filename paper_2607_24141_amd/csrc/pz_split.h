@@ -289,7 +289,8 @@ __device__ __forceinline__ void dev_opacity_near(const StarDev& s, int tile, int
             lo = max(lo, ic - (int)w);
             hi = min(hi, ic + (int)w);
         }
-        unsigned long long m = __builtin_amdgcn_ballot_w64(b + lane < l1 && lo <= p0 + 7 && hi >= p0);
+        // (a line between two pixels can have none in its window: lo > hi)
+        unsigned long long m = __builtin_amdgcn_ballot_w64(b + lane < l1 && lo <= hi && lo <= p0 + 7 && hi >= p0);
         const unsigned long long wide = __builtin_amdgcn_ballot_w64(xf < 0.0f);
         while (m) {
             const int k = __builtin_ctzll(m);
