@@ -145,7 +145,7 @@ __device__ __forceinline__ void dev_line_consts(const StarDev& s, int l, const D
     const int sp = s.ln.spion[l] >> 1;
     const double gam = fma(c.w, bnd.npert, fma(c.z, bnd.ne, c.y));           // >= a dv at every depth
     // damping-ratio range over depth: flags lines whose wavefronts can mix near and far wing tiers
-    bool wide = false;
+    bool wide = false, huge = false;
     if (gam * bnd.inv_dv > 1.0e3) {                        // else a <= 1000 at every depth
         double amin = 1e300, amax = 0.0;
         for (int j = 0; j < s.D; ++j) {
@@ -154,6 +154,7 @@ __device__ __forceinline__ void dev_line_consts(const StarDev& s, int l, const D
             amax = fmax(amax, a);
         }
         wide = (amin < 8.0 && amax > 1.0e3) || (amin < 40.0 && amax > 3.0e4);
+        huge = amax > 4.0e3;                               // a^10 of far_poly's polynomials: 3.5e37 there, past float32 at 5000
     }
     if (s.split) {
         // Far zone: v = x c / dv >= FAR_V at the widest dv, and a <= FAR_AV v,
@@ -161,7 +162,7 @@ __device__ __forceinline__ void dev_line_consts(const StarDev& s, int l, const D
         const double xi = (double)s.xi[0] * 1.0e5;
         const double dv = sqrt(2.0 * K_BOLTZ * bnd.T / (s.mass[sp] * AMU_G) + xi * xi);
         float xfar = (float)(fmax(PZ_FAR_V * dv, gam / PZ_FAR_AV) / C_LIGHT * (1.0 + 1.0e-6));
-        if (!(xfar < window_reach(s, lam))) xfar = INFINITY;   // no far pixel in the window (or not a number)
+        if (huge || !(xfar < window_reach(s, lam))) xfar = INFINITY;   // no far pixel in the window (or not a number)
         s.xfar[l] = wide ? -1.0f : xfar;
     } else {
         s.wide_a[l] = wide ? 1 : 0;
