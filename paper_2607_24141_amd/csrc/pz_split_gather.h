@@ -33,10 +33,18 @@ __device__ __forceinline__ float3 family_shares(const StarDev& s, const double4&
 // sorted lines' windows nearly coincide, and a chunk of 16 pixels is four
 // k-steps (lane (r, c) = (lane / 16, lane % 16): line c and pixels 4 r + t, t =
 // 0..3, of the chunk; B is a float4 of dL/dkappa at depth c).  Chunks with no
-// far pixel are skipped; powers are dropped as in dev_opacity_far.
+// far pixel are skipped.
+// Powers whose terms cannot reach 1e-6 of X at a chunk's nearest pixel are left
+// out: X has lost its leading order and needs one power more than H does (H and
+// a dH/da lose less than 2e-9).  Measured in units of x0, where v >= 5.5 and
+// a <= 0.2 v: n <= 5 from v = 16, n <= 4 from 25, n <= 3 from 74.  With all six
+// X is within 1.8e-5 (at v = 5.5; the direct gather's far-wing series: 9e-5).
 // Two wavefronts share the lines and split the depth tiles (three and two), so
 // the powers' sums fit beside a chunk's operands and the next chunk's loads;
 // the second hands its line sums over through LDS.
+static constexpr float kGFarU5 = 0.12f;                   // (5.5/16)^2
+static constexpr float kGFarU4 = 0.05f;                   // (5.5/25)^2
+static constexpr float kGFarU3 = 0.0055f;                 // (5.5/74)^2
 static constexpr int GFAR_LINES = 16;
 static constexpr int GFAR_NDT = 3;                        // depth tiles per wavefront
 static_assert(2 * GFAR_NDT >= FAR_NDT, "two wavefronts cover the depths");
@@ -124,13 +132,13 @@ __device__ __forceinline__ void dev_gather_far(const StarDev& s, int base, int h
                 for (int t = 0; t < 4; ++t)
                     if (!(fabsf(g[d][t]) < INFINITY)) g[d][t] = 0.0f;
         }
-        gather_powers<0, 2>(T, A, u, g, ndt);
-        if (!wave_any(um > kFarU2)) continue;
-        gather_powers<2, 3>(T, A, u, g, ndt);
-        if (!wave_any(um > kFarU3)) continue;
+        gather_powers<0, 3>(T, A, u, g, ndt);
+        if (!wave_any(um > kGFarU3)) continue;
         gather_powers<3, 4>(T, A, u, g, ndt);
-        if (!wave_any(um > kFarU4)) continue;
-        gather_powers<4, PZ_FAR_N>(T, A, u, g, ndt);
+        if (!wave_any(um > kGFarU4)) continue;
+        gather_powers<4, 5>(T, A, u, g, ndt);
+        if (!wave_any(um > kGFarU5)) continue;
+        gather_powers<5, PZ_FAR_N>(T, A, u, g, ndt);
     }
     // lane (r, c) holds lines base + 4 r + q, q = 0..3, at depths 16 (d0 + d) + c
     const float xi_f = s.xi[0] * (float)(1.0e10 / (C_LIGHT * C_LIGHT));

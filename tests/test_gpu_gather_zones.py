@@ -54,3 +54,27 @@ def test_one_form_of_the_damping_derivative(gpu_lib, v0):
     err = np.abs(a[1] - b[1][:L]) / terms
     print("damping gradients at v = %g, split against direct: %.1e" % (v0, err.max()))
     assert np.all(terms > 0) and err.max() <= 2.4e-7
+
+
+@pytest.mark.parametrize("vmin", [17.0, 27.0, 90.0])
+def test_microturbulence_gradient_far_out(gpu_lib, vmin):
+    """dL/dxi from pixels where every line in reach has v >= vmin at every
+    depth.  Its leading order in 1/v^2 cancels, so a power of the far zone's
+    sum that H can do without shows here first.  The lines are weak and the
+    seed positive, so the terms have one sign: each is good to 2e-6 (the powers
+    left out 1e-6, float32 coefficients and products 1e-6), dL/dkappa and the
+    sums' rounding (thousands of terms in float32) take the rest of 1e-5."""
+    wl = W.tiny(seed=15, L=16, N=3001, D=24, S=4, xi=1.3, lam_lo=500.0, window_nm=4.0)
+    lam = O.wavelengths_nm(wl.grid)
+    wl.lines.lam0_nm[:] = np.random.default_rng(15).uniform(lam[1400], lam[1420], 16)
+    wl.lines.loggf[:] = -6.0
+    v = np.abs(_detunings(wl)).min(axis=(0, 2))
+    i = np.arange(3001)
+    s = np.where((v >= vmin) & (v < 2.0 * vmin + 20.0) & (np.abs(i - 1410) < 1300), 1.0, 0.0).astype(np.float32)
+    assert s.sum() > 20
+    g = gpu_vjp(gpu_lib, wl, s)
+    ref = O.adjoint(wl, wl.params, s.astype(np.float64))
+    err = abs(g[3][0] - ref["g_xi"]) / abs(ref["g_xi"])
+    print("dL/dxi from v >= %g: relative error %.1e" % (vmin, err))
+    assert err <= 1e-5
+    np.testing.assert_allclose(g[0], ref["g_loggf"], rtol=1e-5)
