@@ -37,8 +37,9 @@ enum Phase {
     PH_FAR4,       // (star, 64-pixel tile): ... with long ones
     PH_SEED,       // (star, 512 pixels): chi^2 seed for stars with a target
     PH_LOSS,       // (star): chi^2 value, one 1024-thread workgroup
-    PH_ROWS,       // (star, ROW_ITEM pixels): transfer, one list for each row_list()
-    PH_ROWS_END = PH_ROWS + 7,
+    PH_FLUX,       // (star, ROW_ITEM pixels): transfer, one list for each transfer_list()
+    PH_REVERSE = PH_FLUX + 10,   // ... its adjoint
+    PH_REVERSE_END = PH_REVERSE + 9,
     PH_GATHER,     // (star, GATHER_ITEM lines), atomic queue
     PH_GSPLIT,     // (star, GATHER_ITEM lines) of stars with split sums, atomic queue
     PH_SCATTER,    // (star, 512 lines)
@@ -50,8 +51,12 @@ enum Phase {
 constexpr int PARAM_ITEM = 512 * 32;
 constexpr int N_COUNTER = 5;             // queues: opacity x 3 tile widths, gather, split gather
 constexpr int GATHER_ITEM = 64;
-constexpr int ROW_ITEM = 64;             // pixels of a transfer item: four passes of 16
-int row_list(const pz::StarDev& s) { return PH_ROWS + 2 * (pz::row_np(s.D) - 2) + (s.quad == PZ_QUAD_E2); }
+constexpr int ROW_ITEM = 64;             // pixels of a transfer item: four passes of 16 by rows, one by columns
+// Lists 2 (np - 2) + E2 by rows with np depths per lane, 8 + E2 by columns: what the star's own calls take.
+int transfer_list(const pz::StarDev& s, bool reverse) {
+    const bool e2 = s.quad == PZ_QUAD_E2;
+    return (reverse ? PH_REVERSE : PH_FLUX) + (pz::columns_rule(s.N, s.D, s.quad, reverse) ? 8 : 2 * (pz::row_np(s.D) - 2)) + e2;
+}
 
 // Next item of an atomic queue for the whole workgroup (wavefront-uniform).
 __device__ __forceinline__ int next_item(int* ctr, int* s_it) {
@@ -188,6 +193,22 @@ __global__ __launch_bounds__(256) void kb_flux(const StarDev* __restrict__ stars
 #pragma unroll 1
     for (int k = w.y * ROW_ITEM; k < min((w.y + 1) * ROW_ITEM, s.N); k += FLUX_PX) dev_flux_block(s, k, lds);
 }
+
+// One thread per pixel; blockIdx.y: the branch.
+template <bool E2>
+__global__ __launch_bounds__(WAVE) void kb_flux_column(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ float col[MAXD * WAVE];
+    const int2 w = uniform_item(items, blockIdx.x);
+    dev_flux_columns<E2>(stars[w.x], w.y * ROW_ITEM + threadIdx.x, blockIdx.y == 0, col + threadIdx.x);
+}
+
+template <bool E2>
+__global__ __launch_bounds__(WAVE) void kb_reverse_column(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+    __shared__ double col[MAXD * WAVE];
+    const int2 w = uniform_item(items, blockIdx.x);
+    dev_reverse_columns<E2>(stars[w.x], w.y * ROW_ITEM + threadIdx.x, col + threadIdx.x);
+}
+static_assert(ROW_ITEM == WAVE, "an item by columns is one wavefront");
 
 __global__ __launch_bounds__(512) void kb_seed(const StarDev* __restrict__ stars, const int2* __restrict__ items, int n, const float* inv_s2,
                                                const float* const* ys) {
@@ -357,18 +378,28 @@ static void batch_opacity(const pz_batch* bt, hipStream_t st) {
 }
 
 template <bool REV>
-static void batch_rows(const pz_batch* bt, hipStream_t st) {
+static void batch_transfer(const pz_batch* bt, hipStream_t st) {
+    constexpr int PH = REV ? PH_REVERSE : PH_FLUX;
+    const int* n = bt->n_items + PH;
+    int2* const* it = bt->items + PH;
     for (int np = 2; np <= 5; ++np)
         with_row_np(16 * np, [&](auto NP) {
-            const int g = PH_ROWS + 2 * (np - 2), e = g + 1;
-            if (bt->n_items[g]) {
+            const int g = 2 * (np - 2), e = g + 1;
+            if (n[g]) {
                 if constexpr (REV)
-                    kb_rows<NP.value, false, true><<<bt->n_items[g], 256, 0, st>>>(bt->stars, bt->items[g]);
+                    kb_rows<NP.value, false, true><<<n[g], 256, 0, st>>>(bt->stars, it[g]);
                 else
-                    kb_flux<<<bt->n_items[g], 256, 0, st>>>(bt->stars, bt->items[g]);
+                    kb_flux<<<n[g], 256, 0, st>>>(bt->stars, it[g]);
             }
-            if (bt->n_items[e]) kb_rows<NP.value, true, REV><<<bt->n_items[e], 256, 0, st>>>(bt->stars, bt->items[e]);
+            if (n[e]) kb_rows<NP.value, true, REV><<<n[e], 256, 0, st>>>(bt->stars, it[e]);
         });
+    if constexpr (REV) {
+        if (n[8]) kb_reverse_column<false><<<n[8], WAVE, 0, st>>>(bt->stars, it[8]);
+        if (n[9]) kb_reverse_column<true><<<n[9], WAVE, 0, st>>>(bt->stars, it[9]);
+    } else {
+        if (n[8]) kb_flux_column<false><<<dim3(n[8], 2), WAVE, 0, st>>>(bt->stars, it[8]);
+        if (n[9]) kb_flux_column<true><<<dim3(n[9], 2), WAVE, 0, st>>>(bt->stars, it[9]);
+    }
 }
 
 extern "C" {
@@ -426,7 +457,8 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
         if (st.y)
             for (int k = 0; k < (s.N + 511) / 512; ++k) items[PH_SEED].push_back({b, k});
         if (!s.scatter)
-            for (int k = 0; k < (s.N + ROW_ITEM - 1) / ROW_ITEM; ++k) items[row_list(s)].push_back({b, k});
+            for (int k = 0; k < (s.N + ROW_ITEM - 1) / ROW_ITEM; ++k)
+                for (bool rev : {false, true}) items[transfer_list(s, rev)].push_back({b, k});
         if (st.y && st.loss) items[PH_LOSS].push_back({b, 0});
         for (int k = 0; k < (s.L + GATHER_ITEM - 1) / GATHER_ITEM; ++k) items[s.split_gather ? PH_GSPLIT : PH_GATHER].push_back({b, k});
         for (int k = 0; k < (s.L + 511) / 512; ++k) items[PH_SCATTER].push_back({b, k});
@@ -535,7 +567,7 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
         batch_opacity<true>(bt, st);
     else
         batch_opacity<false>(bt, st);
-    batch_rows<false>(bt, st);
+    batch_transfer<false>(bt, st);
     for (const StarDev& s : bt->sc_stars) {
         const hipError_t e = launch_flux(s, st);
         if (e != hipSuccess) return set_error(PZ_E_HIP, hipGetErrorString(e));
@@ -546,7 +578,7 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
         kb_loss<<<grid(bt->grid1024, n[PH_LOSS]), 1024, 0, st>>>(bt->stars, it[PH_LOSS], n[PH_LOSS], bt->inv_s2,
                                                                  bt->ys, bt->losses);
     if (mode == PZ_MODE_FWD_BWD) {
-        batch_rows<true>(bt, st);
+        batch_transfer<true>(bt, st);
         for (const StarDev& s : bt->sc_stars) {
             const hipError_t e = launch_reverse_scan(s, st);
             if (e != hipSuccess) return set_error(PZ_E_HIP, hipGetErrorString(e));

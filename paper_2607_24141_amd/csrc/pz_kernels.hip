@@ -133,60 +133,18 @@ __global__ __launch_bounds__(256) void k_reverse_scatter(StarDev s) {
     dev_reverse_scatter<NP>(s, blockIdx.x * 16 + threadIdx.x / 16);
 }
 
-// The formal solutions walked by one thread, for a single column: the same
-// segments, in the same order, as dev_flux_block and dev_flux_e2_row.
-struct Ray3 {
-    float F[3], A[3];
-    __device__ void top(float S0, float S1, float t0, float t1) {
-        const float S_top = S0 - t0 * (S1 - S0) / (t1 - t0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const ExpTerms et = exp_terms(t0 * c_inv_mu[k], false);
-            F[k] = fmaf(S_top, et.om, (S0 - S_top) * et.lw);
-            A[k] = et.e;
-        }
-    }
-    __device__ void seg(float Sa, float Sb, float ta, float tb) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const ExpTerms et = exp_terms((tb - ta) * c_inv_mu[k], false);
-            const float c = fmaf(Sa, et.om, (Sb - Sa) * et.lw);
-            F[k] = fmaf(A[k], c, F[k]);
-            A[k] *= et.e;
-        }
-    }
-    __device__ float bottom(float Sa, float Sb, float ta, float tb) {
-        const float grad = (Sb - Sa) / (tb - ta);
-        float out = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const float ID = fmaf(c_mu[k], grad, Sb);
-            out = fmaf(c_wmu[k], fmaf(A[k], ID, F[k]), out);
-        }
-        return out;
-    }
-};
+// One thread per pixel; blockIdx.y: the branch.
+template <bool E2>
+__global__ __launch_bounds__(WAVE) void k_flux_column(StarDev s) {
+    __shared__ float col[MAXD * WAVE];
+    dev_flux_columns<E2>(s, blockIdx.x * WAVE + threadIdx.x, blockIdx.y == 0, col + threadIdx.x);
+}
 
-struct RayE2 {
-    double F, E3a, E4a;
-    __device__ void start() {
-        F = 0.0;
-        E3a = 0.5;            // E3(0)
-        E4a = 1.0 / 3.0;      // E4(0)
-    }
-    __device__ void seg(double Sa, double Sb, double ta, double tb) {
-        double E3b, E4b;
-        expint34(tb, E3b, E4b);
-        const double sl = (Sb - Sa) / (tb - ta);
-        F += Sa * (E3a - E3b) + sl * (E4a - E4b - (tb - ta) * E3b);
-        E3a = E3b;
-        E4a = E4b;
-    }
-    __device__ double bottom(double Sa, double Sb, double ta, double tb) const {
-        const double sD = (Sb - Sa) / (tb - ta);
-        return 2.0 * PI * (F + Sb * E3a + sD * E4a);
-    }
-};
+template <bool E2>
+__global__ __launch_bounds__(WAVE) void k_reverse_column(StarDev s) {
+    __shared__ double col[MAXD * WAVE];
+    dev_reverse_columns<E2>(s, blockIdx.x * WAVE + threadIdx.x, col + threadIdx.x);
+}
 
 __global__ void k_debug_formal(int D, int n, const float* S, const float* tau, int quad, float* F) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -361,6 +319,11 @@ hipError_t launch_opacity(const StarDev& s, int chunk, hipStream_t st) {
 
 hipError_t launch_flux(const StarDev& s, hipStream_t st) {
     const unsigned n = (s.N + 15) / 16;
+    if (!s.scatter && columns_rule(s.N, s.D, s.quad, false)) {
+        const dim3 grid((s.N + WAVE - 1) / WAVE, 2);
+        s.quad == PZ_QUAD_E2 ? k_flux_column<true><<<grid, WAVE, 0, st>>>(s) : k_flux_column<false><<<grid, WAVE, 0, st>>>(s);
+        return hipGetLastError();
+    }
     with_row_np(s.D, [&](auto np) {
         if (s.scatter)
             k_flux_scatter<np.value><<<dim3(n, 2), 256, 0, st>>>(s);
@@ -374,6 +337,11 @@ hipError_t launch_flux(const StarDev& s, hipStream_t st) {
 
 hipError_t launch_reverse_scan(const StarDev& s, hipStream_t st) {
     const unsigned n = (s.N + 15) / 16;
+    if (!s.scatter && columns_rule(s.N, s.D, s.quad, true)) {
+        const unsigned grid = (s.N + WAVE - 1) / WAVE;
+        s.quad == PZ_QUAD_E2 ? k_reverse_column<true><<<grid, WAVE, 0, st>>>(s) : k_reverse_column<false><<<grid, WAVE, 0, st>>>(s);
+        return hipGetLastError();
+    }
     with_row_np(s.D, [&](auto np) {
         if (s.scatter)
             k_reverse_scatter<np.value><<<n, 256, 0, st>>>(s);

@@ -300,6 +300,18 @@ __device__ __forceinline__ float planck(const PixelSetup& p, float invT) {
     return p.c1 / expm1f(p.c2 * invT);
 }
 
+struct PixelSetup64 {
+    double kc, c1, c2;                                    // as PixelSetup
+    __device__ __forceinline__ double planck(double T) const { return c1 / expm1(c2 / T); }
+};
+
+__device__ __forceinline__ PixelSetup64 pixel_setup64(const StarDev& s, int i) {
+    const double lnl = s.ln_first + (double)i * s.h;
+    const double lam_cm = exp(lnl) * 1.0e-7, l2 = lam_cm * lam_cm;
+    return {s.kappa0 * exp(s.alpha * (lnl - s.ln_ref)), 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7,
+            H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ)};
+}
+
 // Both fluxes of the FLUX_PX pixels from i0 by a workgroup of 256, float32.
 // What costs, the exponentials of a segment on three rays and two branches, is
 // independent of the other segments and is spread over all lanes, sixteen
@@ -419,16 +431,12 @@ struct RowPixel64 {
         q = threadIdx.x & 15;
         kd = (D - 1) % NP;
         last = q == (D - 1) / NP;
-        const double lnl = s.ln_first + (double)i * s.h;
-        const double lam_cm = exp(lnl) * 1.0e-7;
-        kc = s.kappa0 * exp(s.alpha * (lnl - s.ln_ref));
-        const double l2 = lam_cm * lam_cm;
-        const double c1 = 2.0 * H_PLANCK * C_LIGHT * C_LIGHT / (l2 * l2 * lam_cm) * 1.0e-7;
-        const double c2 = H_PLANCK * C_LIGHT / (lam_cm * K_BOLTZ);
+        const PixelSetup64 p = pixel_setup64(s, i);
+        kc = p.kc;
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
             const int j = min(depth(k), D - 1);
-            S[k] = c1 / expm1(c2 / s.T[j]);
+            S[k] = p.planck(s.T[j]);
             chi[k] = kc + (double)s.kappa[(size_t)j * s.Npad + i];
             dm[k] = j == 0 ? s.m[0] : s.m[j] - s.m[j - 1];
         }
@@ -747,6 +755,12 @@ __device__ __forceinline__ void dev_reverse_row(const StarDev& s, int i) {
     row_dchi<NP>(s, x.q, gt);
     if (px) row_store_gk<NP>(s, x.q, i, gt);
 }
+
+}  // namespace pz
+
+#include "pz_columns.h"
+
+namespace pz {
 
 // Calls f with the depths per lane of D as a compile-time constant.
 template <class F>
