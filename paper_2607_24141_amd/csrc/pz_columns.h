@@ -328,7 +328,7 @@ inline bool columns_rule(int N, int D, int quad, bool reverse) {
         return reverse ? flights * (6.0 + 0.87 * D) < 7.0 + 2.35e-4 * n * np
                        : std::max(1.0, 0.6 + n / 50000.0) * (5.0 + 0.79 * D) < 7.0 + 3.35e-4 * n * np;
     return reverse ? flights * (7.0 + 1.55 * D) < 8.0 + 5.2e-4 * n * np
-                   : std::max(1.0, 0.7 + n / 70000.0) * (5.6 + 0.62 * D) <
+                   : flights * (5.9 + 0.65 * D) <
                          7.0 + 0.155 * D + std::max(0.0, n - 12000.0) * (9.5e-5 + 6.5e-5 * chunks + 6.2e-6 * D);
 }
 
