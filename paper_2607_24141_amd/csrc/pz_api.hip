@@ -111,14 +111,27 @@ bool split_rule(int N, int L, int D, int64_t evals) {
     return per_px <= 2.0 || (N >= 8000 && (window_px >= 165.0 || per_px <= 5.5));
 }
 
-// Whether the gather of a split plan is split too (pz_split_gather.h).  With
-// the centre test most lines of a dense catalogue are cut inside their window
-// at some depth, have no far zone and are summed directly either way: at 4.8
-// lines per pixel (120,000 lines, 1560-1700 nm) the split gather takes 0.98 ms
-// and the direct one 1.03, so those plans keep the direct one, with the
-// rounding of its ill-conditioned sums; sparse catalogues, and all plans
-// without the centre test, gain (1500-1700 nm: 1.05 against 1.93 ms).
-bool split_gather_rule(int N, int L, bool center) { return !center || L <= N; }
+// Whether the gather of a split plan is split too (pz_split_gather.h).
+// Its far pass walks the union of sixteen neighbouring lines' windows, about
+// window + 15 N / L pixels: they have to overlap, and to reach well beyond the
+// near zone, which the direct gather passes anyway.  Fewer than about 8,000
+// lines do not fill the chip, and the walk's length is what counts.  Split
+// against direct, 72 depths (us; in brackets the lines over a pixel):
+//   113 px: 3,000 lines 75 / 61 (35), 109 / 62 (9); 10,000 lines 126 / 135 (30);
+//           100,000 lines 891 / 951 (17); 30,000 lines 402 / 308 (5);
+//   360 px: 1,000 lines 107 / 122 (35), 180 / 121 (9), 582 / 147 (0.5);
+//           30,000 lines 446 / 690 (15); 10,000 lines 335 / 452 (5);
+//   3,600 px: 3,000 lines 783 / 1412 (16), 100 lines 893 / 1022 (9), 300 lines 2371 / 1290 (1.5);
+//   60 px: 30,000 lines 237 / 233 (45), 10,000 lines 116 / 93 (15).
+// With the centre test most lines of a dense catalogue are cut inside their
+// window at some depth, have no far zone and are summed directly either way,
+// so dense plans keep the direct gather (120,000 lines, 1560-1700 nm: 1.03 ms).
+bool split_gather_rule(int N, int L, int D, int64_t evals, bool center) {
+    if (L == 0 || (center && L > N)) return false;
+    const double window_px = (double)evals / D / L, over_px = window_px * L / N;
+    if (L >= 8000) return window_px >= 100.0 && over_px >= (window_px >= 200.0 ? 5.0 : 16.0);
+    return window_px >= 160.0 && over_px >= (window_px >= 1000.0 ? 10.0 : 25.0);
+}
 
 }  // namespace
 
@@ -359,7 +372,7 @@ int pz_plan_create(const pz_grid* grid, const pz_lines* lines, int32_t n_species
     p->tile_order = (int*)(base + o_order);
     p->qctr = (int*)(base + o_qctr);
     p->split = split;
-    p->split_gather = split && split_gather_rule(N, L, opts->center_eta > 0.0);
+    p->split_gather = split && split_gather_rule(N, L, D, evals, opts->center_eta > 0.0);
     p->n_t32 = n_t32;
     p->t32_first = (int*)(base + o_t32f);
     p->t32_last = (int*)(base + o_t32l);

@@ -275,6 +275,7 @@ __device__ __forceinline__ void dev_opacity_near(const StarDev& s, int tile, int
         off[g] = (unsigned)min(j0 + 8 * g, D - 1) * 16u;
         acc[g] = 0.0f;
     }
+    bool some = false;                                    // a line in reach of the wavefront's pixels
     for (int b = l0; b < l1; b += WAVE) {
         const int l = min(b + lane, l1 - 1);
         const float xf = s.xfar[l];
@@ -292,6 +293,7 @@ __device__ __forceinline__ void dev_opacity_near(const StarDev& s, int tile, int
         // (a line between two pixels can have none in its window: lo > hi)
         unsigned long long m = __builtin_amdgcn_ballot_w64(b + lane < l1 && lo <= hi && lo <= p0 + 7 && hi >= p0);
         const unsigned long long wide = __builtin_amdgcn_ballot_w64(xf < 0.0f);
+        some = some || m;
         while (m) {
             const int k = __builtin_ctzll(m);
             m &= m - 1;
@@ -316,7 +318,7 @@ __device__ __forceinline__ void dev_opacity_near(const StarDev& s, int tile, int
             }
         }
     }
-    if (i < s.N) {
+    if (some && i < s.N) {
 #pragma unroll
         for (int g = 0; g < NG; ++g)
             if (j0 + 8 * g < D) s.kappa[(size_t)(j0 + 8 * g) * s.Npad + i] += acc[g];

@@ -118,7 +118,19 @@ __device__ __forceinline__ void dev_gather_far(const StarDev& s, int base, int h
             um = fmaxf(um, u[t]);
             A[t] = u[t];
         }
-        if (!wave_any(um > 0.0f)) continue;
+        if (!wave_any(um > 0.0f)) {
+            // to the next pixel of any of the lines' windows (they need not overlap)
+            int to = hi >= i + 16 ? max(lo, i + 16) : s.N;
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) to = min(to, __shfl_xor(to, o, WAVE));
+            to = __builtin_amdgcn_readfirstlane(to) & ~15;
+            if (to > i + 16 && to <= i1) {
+                i = to - 16;                              // the loop's step follows
+#pragma unroll
+                for (int d = 0; d < GFAR_NDT; ++d) next[d] = *(const f32x4*)(gp[d] + to);
+            }
+            continue;
+        }
         if (wave_any(!(fin.x + fin.y + fin.z + fin.w == 0.0f))) {
             // a non-finite g reaches the lines whose far zone holds its pixel and no others
 #pragma unroll
