@@ -329,6 +329,7 @@ struct pz_batch {
     float** losses;
     int* ctr;             // [N_COUNTER] queue counters: opacity (32, 64, 128), gather, split gather
     int grid512, grid256, grid1024, grid_op[3], grid_gather;
+    bool halves64;        // 64-pixel opacity tiles in halves
     void* base;
 };
 
@@ -349,17 +350,16 @@ static void batch_opacity_main(const pz_batch* bt, int n, const int2* items, int
         kb_opacity<WPX, ANYCT, GB - 1, false, NTH><<<grid, NTH, 0, st>>>(bt->stars, items, n, ctr);
 }
 
-// A batch with fewer than two tiles per workgroup slot is over when its
-// heaviest tiles are (8.3 ms for 885 tiles of five stars, 3.9 of issue): those
-// go out as two workgroups of four wavefronts each, which spreads a heavy
-// tile's wavefronts over twice the SIMDs (an eight-star batch forward +
-// backward: 17.8 ms against 20.1; parts of two wavefronts, whose staging of
-// every line serves only 16 pixels, 22.4).  The wavefronts do what they do in
-// a whole tile, so the results are the same bits.
+// Tiles in halves as in the per-star launches (the same bits either way).
+// 64-pixel tiles gain where the heaviest one outlasts the chip's share of the
+// rest: the items' costs add up to less than half of slots x the heaviest.
+// Eight stars of unlike line densities (888 tiles, 0.44 of it) take 17.8 ms
+// forward + backward in halves, 20.1 whole and 22.4 in quarters; alike stars
+// of 440 tiles (0.53) 1132 us forward whole and 1246 in halves (40 depths).
 template <int WPX, bool ANYCT>
 static void batch_opacity_wpx(const pz_batch* bt, int n, const int2* items, int* ctr, int grid, hipStream_t st) {
-    if (n < 2 * grid)
-        batch_opacity_main<WPX, ANYCT, 256>(bt, n, items, ctr, 2 * grid, st);
+    if (opacity_halves<WPX, ANYCT>(bt->halves64))
+        batch_opacity_main<WPX, ANYCT, opacity_half_threads<WPX, ANYCT>()>(bt, n, items, ctr, 2 * grid, st);
     else
         batch_opacity_main<WPX, ANYCT, 512>(bt, n, items, ctr, grid, st);
     kb_opacity_wide<WPX, ANYCT><<<grid, 512, 0, st>>>(bt->stars, items, n);
@@ -529,6 +529,13 @@ int pz_batch_create(int32_t n_star, const pz_star* stars, pz_batch** out) {
     }
     for (int k = 0; k < 3; ++k) bt->grid_op[k] = std::max(1, n_cu * std::max(occ_op[k], 1));
     bt->grid_gather = std::max(1, n_cu * std::max(occ_g, 1));
+    double cost = 0.0, heaviest = 0.0;
+    for (const int2& w : items[PH_OP64]) {
+        const double c = (double)stars[w.x].plan->tile_cost[w.y];
+        cost += c;
+        heaviest = std::max(heaviest, c);
+    }
+    bt->halves64 = 2.0 * cost <= heaviest * bt->grid_op[1];
     bt->grid512 = std::max(1, n_cu * 4);
     bt->grid256 = std::max(1, n_cu * 8);
     bt->grid1024 = std::max(1, n_cu * 2);

@@ -273,17 +273,21 @@ static void launch_opacity_parts(const StarDev& s, int chunk, hipStream_t st) {
         k_opacity<WPX, CT, GB - 1, false, NTH><<<grid, NTH, 0, st>>>(s, chunk);
 }
 
-// With fewer tiles than the chip holds, a tile goes to two workgroups of half
-// its wavefronts each, which stage the lines for themselves: the sums and their
-// order stay the same.  64-pixel tiles, forward calls at 72 depths, whole
+// A tile in two workgroups of half its wavefronts each, which stage the lines
+// for themselves: the sums and their order stay the same.  64-pixel tiles gain
+// where all halves are in flight at once (three on a CU, as whole tiles: half
+// as many tiles as the chip holds, 384); forward calls at 72 depths, whole
 // against halves: 16 tiles 815 and 711 us, 69 949 and 835, 124 980 and 851, 188
-// 1506 and 1264, 313 1646 and 1300; 579 (more than the 512 the chip holds)
-// 2021 and 2121.  Quarters gain nothing more, and 32-pixel tiles (137: 543 and
-// 555 us) nothing at all.
+// 1506 and 1264, 352 1647 and 1298; 400 1678 and 1875, 579 2021 and 2121 (8
+// depths: 352 703 and 586, 400 739 and 1008).  Quarters gain nothing more, and 32-pixel tiles (137: 543 and 555 us) nothing
+// at all.  128-pixel tiles: without the centre test the staging of every line
+// twice costs more than the spread gives (7,000 pixels, 25,000 lines: 72 depths
+// 1623 and 1661 us, 8 depths 592 and 669); with it eight wavefronts' registers
+// spill and four's do not (3237 and 1307).
 template <int WPX, bool CT>
 static void launch_opacity_wpx(const StarDev& s, int chunk, int grid, hipStream_t st) {
-    if (WPX > 4 && 3 * s.n_tiles <= 2 * s.grid_opacity)
-        launch_opacity_parts<WPX, CT, WPX == 4 ? 512 : 256>(s, chunk, st);
+    if (opacity_halves<WPX, CT>(2 * s.n_tiles <= s.grid_opacity))
+        launch_opacity_parts<WPX, CT, opacity_half_threads<WPX, CT>()>(s, chunk, st);
     else
         launch_opacity_parts<WPX, CT, 512>(s, chunk, st);
     k_opacity_wide<WPX, CT><<<grid, 512, 0, st>>>(s, chunk);

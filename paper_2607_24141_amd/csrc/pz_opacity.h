@@ -425,4 +425,15 @@ __device__ __forceinline__ void dev_opacity_tile(const StarDev& s, int tile, int
         opacity_tile_body<WPX, false, WIDE, G, PAIRED, FG, NTH>(s, tile, sub, chunk, sm);
 }
 
+// Whether tiles go out in halves (see launch_opacity_wpx; few: 64-pixel tiles
+// do not fill the chip), and the threads of a half where that is ever so.
+template <int WPX, bool CT>
+constexpr bool opacity_halves(bool few) {
+    return WPX == 8 ? few : WPX == 16 && CT;
+}
+template <int WPX, bool CT>
+constexpr int opacity_half_threads() {
+    return WPX == 8 || (WPX == 16 && CT) ? 256 : 512;
+}
+
 }  // namespace pz
