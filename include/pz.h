@@ -352,7 +352,9 @@ int synth_batch(const pz_batch* batch, int32_t mode, pz_stream stream);
 /* Autotuner: times synth_forward for every supported (tile_px,
  * lines_per_chunk) pair on the given inputs and returns the fastest in
  * *best (other fields copied from *base).  Builds temporary plans and
- * synchronises the device; reps timed forward passes per candidate. */
+ * synchronises the device; reps timed forward passes per candidate.  Where the
+ * plan's line sums are split by detuning the pair has no effect: (32, 16) is
+ * timed and returned. */
 int pz_autotune(const pz_grid* grid, const pz_lines* lines, int32_t n_species, int32_t n_depth,
                 const pz_options* base, const pz_atmos* atm, const pz_params* par, int32_t reps,
                 pz_options* best, float* best_ms);

@@ -627,13 +627,16 @@ int pz_autotune(const pz_grid* grid, const pz_lines* lines, int32_t n_species, i
         hipEventCreate(&e1) != hipSuccess) {
         rc = set_error(PZ_E_NOMEM, "autotune buffers");
     }
-    for (int ti = 0; ti < 3 && rc == PZ_OK; ++ti) {
-        for (int ci = 0; ci < 2 && rc == PZ_OK; ++ci) {
+    bool split = false;                                // the pair has no effect: one is timed, the noise of six not ranked
+    for (int ti = 0; ti < 3 && rc == PZ_OK && !split; ++ti) {
+        for (int ci = 0; ci < 2 && rc == PZ_OK && !split; ++ci) {
             pz_options o = *base;
             o.tile_px = tiles[ti];
             o.lines_per_chunk = chunks[ci];
             pz_plan* p = nullptr;
             if ((rc = pz_plan_create(grid, lines, n_species, n_depth, &o, &p))) break;
+            split = p->split;
+            if (split) o.lines_per_chunk = 16;         // with 32 pixels what direct plans of these sizes take
             if ((rc = synth_forward(p, atm, par, F, F + grid->N, nullptr)) == PZ_OK) {
                 (void)hipEventRecord(e0, nullptr);
                 for (int r = 0; r < reps && rc == PZ_OK; ++r) rc = synth_forward(p, atm, par, F, F + grid->N, nullptr);

@@ -145,3 +145,15 @@ def test_batch_of_direct_stars_bitwise(gpu_lib, tile, chunk, eta, skewed):
         torch.cuda.synchronize()
         for x, y in zip(out, one):
             np.testing.assert_array_equal(x.cpu().numpy(), y.cpu().numpy())
+
+
+def test_autotune_of_split_and_direct_plans(gpu_lib):
+    """A plan that splits its sums does not depend on the pair: the tuner returns
+    the same one each time instead of the fastest of six equal ones."""
+    pz = gpu_lib
+    for wl, want in ((W.tiny(seed=9, L=300, N=3000, D=24), {(32, 16)}),
+                     (_dense(300, 700, 24, 84), {(t, c) for t in (32, 64, 128) for c in (8, 16)})):
+        for _ in range(4):
+            tile, chunk, ms = pz.pz_autotune(wl.grid, wl.lines, wl.atm.S, wl.atm.D, pz.Atmos(wl.atm),
+                                             pz.Params.from_host(wl.params), reps=2)
+            assert (tile, chunk) in want and ms > 0
