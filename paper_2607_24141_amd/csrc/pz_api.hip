@@ -89,22 +89,22 @@ Window line_window(double lam_l, double lf, double r1, double h, int N, double W
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Whether a plan's line sums are split by detuning (pz_split.h).
-// The split sums are the faster ones everywhere (1500-1700 nm, 5.3 lines per
-// pixel, 113-pixel windows: 0.90 against 1.26 ms; 300-1000 nm, 180-600 pixels:
-// 32 against 54 ms; eight stars of 1-24 lines per pixel: 4.9 against 9.0 ms).
-// What sends a plan to the direct kernel is the conditioning of its gradients,
-// not its time: with more than ~5.5 lines per pixel and windows this narrow, a
-// star of ordinary abundances is optically thick at its first depth at every
-// wavelength, its line gradients are what is left of surface terms that cancel
-// to 1e-4 and less, and one float32 rounding of kappa moves them by 1e-5 to
-// 1e-4 of their norm (measured on such stars; 1e-7 to 4e-6 at lower
-// densities).  A short grid gets there at 2.2 lines per pixel, whatever its
-// windows, when one molecular band covers all of it: of 170 workloads with
-// 1.5-5.5 lines per pixel, eight moved by more than 2e-5 (up to 2e-4), all but
-// one of them with fewer than 8,000 pixels and more than two lines in each.
-// Neither order of summation is the more exact there, so those plans keep the
-// one their results were always taken with, bit for bit, and its time (4,365
-// pixels, four lines in each, a fitting step: 1.05 ms, under 0.50 if split).
+// The split sums are the faster ones on dense plans too (1500-1700 nm, 5.3
+// lines per pixel, 113-pixel windows: 0.90 against 1.26 ms; 300-1000 nm, 180-600
+// pixels: 32 against 54 ms; a fitting step of 4,365 pixels and four lines in
+// each: 0.42 against 0.95 ms, of 20,000 and eight: 1.9 against 3.2), and as exact: on 24 dense workloads the errors of their
+// gradients against float64 are 0.9-1.04 times the direct sums' (geometric
+// mean).  What keeps some plans direct is that their gradients do not stand
+// another order of summation.  A star that is optically thick at its first
+// depth at every wavelength has line gradients left over from surface terms
+// that cancel to 1e-4 and less; one float32 rounding of kappa moves them by
+// 1e-5 to 1e-4 of their norm (1e-7 to 4e-6 at lower densities).  That takes
+// more than ~5.5 lines per pixel in windows this narrow, and on short grids,
+// which one molecular band can cover, two.  The edges are fitted: of 90
+// workloads of 900-8,000 pixels and 1.2-8 lines in each, six would move by more
+// than 2e-5 of a gradient's norm or 8e-4 of an entry if split, none does by
+// this rule; of 40 of 8,000-37,550 pixels and 1.2-12 lines, four and one (11
+// lines per pixel, 176-pixel windows: 4e-5).
 bool split_rule(int N, int L, int D, int64_t evals) {
     if (L == 0) return true;
     const double window_px = (double)evals / D / L, per_px = (double)L / N;

@@ -138,13 +138,13 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void kb_opacity_wide(con
 
 // Split sums: one workgroup per (star, tile) item; the far zone's form is the
 // one that the star's own calls take.
-__global__ __launch_bounds__(FAR_MAX_WAVES / 2 * WAVE) void kb_opacity_far2(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+__global__ __launch_bounds__(far_waves<2>() * WAVE) void kb_opacity_far2(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
     __shared__ FarLds<2> lds;
     const int2 w = uniform_item(items, blockIdx.x);
     dev_opacity_far<2>(stars[w.x], w.y, lds);
 }
 
-__global__ __launch_bounds__(4 * WAVE) void kb_opacity_far4(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
+__global__ __launch_bounds__(far_waves<4>() * WAVE) void kb_opacity_far4(const StarDev* __restrict__ stars, const int2* __restrict__ items) {
     __shared__ FarLds<4> lds;
     const int2 w = uniform_item(items, blockIdx.x);
     dev_opacity_far<4>(stars[w.x], w.y, lds);
@@ -566,8 +566,8 @@ int synth_batch(const pz_batch* bt, int32_t mode, pz_stream stream) {
     if (n[PH_LINES]) kb_lines<<<grid(bt->grid512, n[PH_LINES]), 512, 0, st>>>(bt->stars, it[PH_LINES], n[PH_LINES]);
     kb_params<<<grid(bt->grid512, n[PH_PARAMS]), 512, 0, st>>>(bt->stars, it[PH_PARAMS], n[PH_PARAMS]);
     if (n[PH_SPLIT]) {
-        if (n[PH_FAR4]) kb_opacity_far4<<<n[PH_FAR4], 4 * WAVE, 0, st>>>(bt->stars, it[PH_FAR4]);
-        if (n[PH_FAR2]) kb_opacity_far2<<<n[PH_FAR2], 8 * WAVE, 0, st>>>(bt->stars, it[PH_FAR2]);
+        if (n[PH_FAR4]) kb_opacity_far4<<<n[PH_FAR4], far_waves<4>() * WAVE, 0, st>>>(bt->stars, it[PH_FAR4]);
+        if (n[PH_FAR2]) kb_opacity_far2<<<n[PH_FAR2], far_waves<2>() * WAVE, 0, st>>>(bt->stars, it[PH_FAR2]);
         kb_opacity_near<<<dim3(n[PH_SPLIT], near_parts(bt->max_d)), 256, 0, st>>>(bt->stars, it[PH_SPLIT]);
     }
     if (bt->any_center)

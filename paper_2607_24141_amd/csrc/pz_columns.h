@@ -17,7 +17,7 @@ struct Ray3 {
         const float S_top = S0 - t0 * (S1 - S0) / (t1 - t0);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const ExpTerms et = exp_terms(t0 * c_inv_mu[k], false);
+            const ExpTerms et = exp_terms(t0 * c_inv_mu[k]);
             F[k] = fmaf(S_top, et.om, (S0 - S_top) * et.lw);
             A[k] = et.e;
         }
@@ -25,7 +25,7 @@ struct Ray3 {
     __device__ void seg(float Sa, float Sb, float ta, float tb) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const ExpTerms et = exp_terms((tb - ta) * c_inv_mu[k], false);
+            const ExpTerms et = exp_terms((tb - ta) * c_inv_mu[k]);
             const float c = fmaf(Sa, et.om, (Sb - Sa) * et.lw);
             F[k] = fmaf(A[k], c, F[k]);
             A[k] *= et.e;

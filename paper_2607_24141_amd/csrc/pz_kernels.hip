@@ -60,7 +60,7 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void k_opacity_wide(Star
 // Split sums: one workgroup per 32-pixel tile, dispatched in order of
 // decreasing cost (longest first: tiles differ several-fold in line count).
 template <int NPT>
-__global__ __launch_bounds__(FAR_MAX_WAVES / 2 * WAVE) void k_opacity_far(StarDev s) {
+__global__ __launch_bounds__(far_waves<NPT>() * WAVE) void k_opacity_far(StarDev s) {
     __shared__ FarLds<NPT> lds;
     dev_opacity_far<NPT>(s, NPT == 2 ? s.t32_order[blockIdx.x] : blockIdx.x, lds);
 }
@@ -307,8 +307,8 @@ static hipError_t launch_opacity_tiles(const StarDev& s, int chunk, int grid, hi
 hipError_t launch_opacity(const StarDev& s, int chunk, hipStream_t st) {
     if (s.n_tiles == 0) return hipSuccess;
     if (s.split) {
-        far_wide(s.n_t32) ? k_opacity_far<4><<<(s.n_t32 + 1) / 2, 4 * WAVE, 0, st>>>(s)
-                          : k_opacity_far<2><<<s.n_t32, 8 * WAVE, 0, st>>>(s);
+        far_wide(s.n_t32) ? k_opacity_far<4><<<(s.n_t32 + 1) / 2, far_waves<4>() * WAVE, 0, st>>>(s)
+                          : k_opacity_far<2><<<s.n_t32, far_waves<2>() * WAVE, 0, st>>>(s);
         const dim3 grid(s.n_t32, near_parts(s.D));
         if (s.center)
             k_opacity_near<true><<<grid, 256, 0, st>>>(s);

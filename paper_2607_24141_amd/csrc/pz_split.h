@@ -42,15 +42,18 @@ static constexpr int FAR_NDT = (MAXD + 15) / 16;         // depth tiles
 static constexpr float kFarU4 = 0.179f;                  // (5.5/13)^2
 static constexpr float kFarU3 = 0.0525f;                 // (5.5/24)^2
 static constexpr float kFarU2 = 0.0041f;                 // (5.5/86)^2
-static constexpr int FAR_MAX_WAVES = 16;
 // Whether a grid of n 32-pixel tiles takes 64 pixels per workgroup.
 __host__ __device__ constexpr bool far_wide(int n) { return n >= 4096; }
 
 // Pixels per workgroup: NPT 16-pixel blocks share a line's coefficients and
 // loads.  Four (64 pixels) where the grid fills the chip, two below that.
 template <int NPT>
+constexpr int far_waves() {
+    return NPT == 2 ? 8 : 4;
+}
+template <int NPT>
 struct FarLds {
-    f32x4 part[FAR_MAX_WAVES / 2][FAR_NDT][WAVE];
+    f32x4 part[far_waves<NPT>() / 2][FAR_NDT][WAVE];
 };
 
 // The window fields and parameter rows of one k-step (four lines).
@@ -111,7 +114,7 @@ __device__ __forceinline__ void far_powers(f32x4 (*acc)[FAR_NDT], float* A, cons
 template <int NPT>
 __device__ __forceinline__ void dev_opacity_far(const StarDev& s, int tile, FarLds<NPT>& lds) {
     const int lane = threadIdx.x % WAVE, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int nw = blockDim.x / WAVE;
+    constexpr int nw = far_waves<NPT>();
     const int c = lane % 16, r = lane / 16;
     constexpr int T32 = NPT / 2;                          // tiles of the line lists
     const int p0 = tile * (16 * NPT);

@@ -260,22 +260,17 @@ __constant__ float c_wmu[3] = {(float)(2.0 * PI * 5.0 / 18.0 * kMu0), (float)(2.
                                (float)(2.0 * PI * 5.0 / 18.0 * kMu2)};  // 2 pi w_k mu_k
 
 struct ExpTerms {
-    float e, om, lw, dlw;   // e^-x, 1 - e^-x, lw(x), lw'(x)
+    float e, om, lw;        // e^-x, 1 - e^-x, lw(x)
 };
 
-__device__ __forceinline__ ExpTerms exp_terms(float x, bool need_d) {
+__device__ __forceinline__ ExpTerms exp_terms(float x) {
     ExpTerms r;
     r.e = expf(-x);
     r.om = -expm1f(-x);
-    if (x < 0.05f) {
-        // series of lw and lw' (sum_{n>=2} (-1)^n (n-1) x^{n-1}/n! and its derivative)
+    if (x < 0.05f)          // series of lw (sum_{n>=2} (-1)^n (n-1) x^{n-1}/n!)
         r.lw = x * fmaf(x, fmaf(x, fmaf(x, fmaf(x, 1.0f / 144.0f, -1.0f / 30.0f), 0.125f), -1.0f / 3.0f), 0.5f);
-        r.dlw = need_d ? fmaf(x, fmaf(x, fmaf(x, fmaf(x, 5.0f / 144.0f, -2.0f / 15.0f), 0.375f), -2.0f / 3.0f), 0.5f) : 0.0f;
-    } else {
-        const float inv = 1.0f / x;
-        r.lw = fmaf(-x, r.e, r.om) * inv;
-        r.dlw = need_d ? fmaf(-r.lw, inv, r.e) : 0.0f;
-    }
+    else
+        r.lw = fmaf(-x, r.e, r.om) * (1.0f / x);
     return r;
 }
 
@@ -321,8 +316,8 @@ __device__ __forceinline__ PixelSetup64 pixel_setup64(const StarDev& s, int i) {
 // thread: gradients of saturated spectra cancel to 1e-4 of their terms, and
 // another order of these sums shows in them.  One thread per pixel and branch
 // needs 72 serial steps with three rays' exponentials in each: 52 us at 1,795
-// pixels, 16 now; 53 against 41 at 20,011; 0.30 ms either way at 361,193, where
-// one lane per pixel fills the chip.
+// pixels, 16 now; 53 against 41 at 20,011.  Where one lane per pixel fills the
+// chip the walk is no slower and dev_flux_column takes it (columns_rule).
 constexpr int FLUX_PX = 16;
 struct FluxLds {
     float kc[FLUX_PX], c1[FLUX_PX], c2[FLUX_PX];
@@ -383,7 +378,7 @@ __device__ __forceinline__ void dev_flux_block(const StarDev& s, int i0, FluxLds
                 }
 #pragma unroll
                 for (int m = 0; m < 3; ++m) {
-                    const ExpTerms et = exp_terms(dt * c_inv_mu[m], false);
+                    const ExpTerms et = exp_terms(dt * c_inv_mu[m]);
                     L.t[b][m][g][px] = make_float2(fmaf(Sa, et.om, (Sb - Sa) * et.lw), et.e);
                 }
             }
@@ -565,8 +560,8 @@ __device__ __forceinline__ void row_expint(int D, int q, const double* dt, doubl
 // Both E2 fluxes of pixel i by a row of lanes, float64: every knot's
 // exponential integrals and every segment are independent, so only the
 // running optical depth and the final sum cross lanes.  12,001 pixels at 72
-// depths: flux 453 us by one thread per pixel, 24 now; adjoint 450 against 17 (194 and
-// 85 before the exponential integrals above were made polynomials).
+// depths: flux 453 us by one thread per pixel and the integrals' series, 194 by
+// rows, 24 with the polynomials above; adjoint 450, 85 and 17.
 template <int NP>
 __device__ __forceinline__ void dev_flux_e2_row(const StarDev& s, int i) {
     const bool px = i < s.N;
@@ -690,7 +685,8 @@ __device__ __forceinline__ ExpTerms64 exp_terms64(double x) {
 // By a row of lanes: a segment's transmission to the surface A_{j-1} is a
 // product over all segments above, one scan per ray; the terms of the
 // segments are then independent (72 depths, 1,795 pixels: 95 us by one thread
-// per pixel, 16 now; 20,011 pixels: 98 against 61).
+// per pixel, 16 now; 20,011 pixels: 98 against 61; from 120,000 pixels on, and
+// at few depths, dev_reverse_column is the faster).
 template <int NP>
 __device__ __forceinline__ void dev_reverse_row(const StarDev& s, int i) {
     const bool px = i < s.N;
