@@ -59,8 +59,10 @@ __global__ __launch_bounds__(512) PZ_OPACITY_WAVES(WPX) void k_opacity_wide(Star
 
 // Split sums: one workgroup per 32-pixel tile, dispatched in order of
 // decreasing cost (longest first: tiles differ several-fold in line count).
+// (One bound for both forms: with its own the wider one takes 94 VGPRs and 80
+// AGPRs, two wavefronts per SIMD, against 156 and three.)
 template <int NPT>
-__global__ __launch_bounds__(far_waves<NPT>() * WAVE) void k_opacity_far(StarDev s) {
+__global__ __launch_bounds__(far_waves<2>() * WAVE) void k_opacity_far(StarDev s) {
     __shared__ FarLds<NPT> lds;
     dev_opacity_far<NPT>(s, NPT == 2 ? s.t32_order[blockIdx.x] : blockIdx.x, lds);
 }

@@ -114,7 +114,7 @@ __device__ __forceinline__ void far_powers(f32x4 (*acc)[FAR_NDT], float* A, cons
 template <int NPT>
 __device__ __forceinline__ void dev_opacity_far(const StarDev& s, int tile, FarLds<NPT>& lds) {
     const int lane = threadIdx.x % WAVE, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    constexpr int nw = far_waves<NPT>();
+    const int nw = blockDim.x / WAVE;                     // far_waves<NPT>()
     const int c = lane % 16, r = lane / 16;
     constexpr int T32 = NPT / 2;                          // tiles of the line lists
     const int p0 = tile * (16 * NPT);

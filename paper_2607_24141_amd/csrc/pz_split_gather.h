@@ -97,7 +97,11 @@ __device__ __forceinline__ void dev_gather_far(const StarDev& s, int base, int h
     f32x4 next[GFAR_NDT];
 #pragma unroll
     for (int d = 0; d < GFAR_NDT; ++d) next[d] = i0 <= i1 ? *(const f32x4*)(gp[d] + i0) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int i = i0; i <= i1; i += 16) {
+    for (int i = i0, nx; i <= i1; i = nx) {
+        // the next chunk that a window reaches: the sorted lines' windows begin and end in order, so the
+        // first line that goes on beyond this chunk has it (none: the end)
+        const unsigned on = (unsigned)__builtin_amdgcn_ballot_w64(hi >= i + 16) & 0xffffu;
+        nx = on ? max(i + 16, __builtin_amdgcn_readlane(lo, __builtin_ctz(on)) & ~15) : i1 + 1;
         f32x4 g[GFAR_NDT];
         f32x4 fin = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -105,9 +109,9 @@ __device__ __forceinline__ void dev_gather_far(const StarDev& s, int base, int h
             g[d] = next[d];
             fin += g[d] * 0.0f;
         }
-        if (i + 16 <= i1)
+        if (nx <= i1)
 #pragma unroll
-            for (int d = 0; d < GFAR_NDT; ++d) next[d] = *(const f32x4*)(gp[d] + i + 16);
+            for (int d = 0; d < GFAR_NDT; ++d) next[d] = *(const f32x4*)(gp[d] + nx);
         float u[4], A[4], um = 0.0f;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -118,19 +122,7 @@ __device__ __forceinline__ void dev_gather_far(const StarDev& s, int base, int h
             um = fmaxf(um, u[t]);
             A[t] = u[t];
         }
-        if (!wave_any(um > 0.0f)) {
-            // to the next pixel of any of the lines' windows (they need not overlap)
-            int to = hi >= i + 16 ? max(lo, i + 16) : s.N;
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) to = min(to, __shfl_xor(to, o, WAVE));
-            to = __builtin_amdgcn_readfirstlane(to) & ~15;
-            if (to > i + 16 && to <= i1) {
-                i = to - 16;                              // the loop's step follows
-#pragma unroll
-                for (int d = 0; d < GFAR_NDT; ++d) next[d] = *(const f32x4*)(gp[d] + to);
-            }
-            continue;
-        }
+        if (!wave_any(um > 0.0f)) continue;
         if (wave_any(!(fin.x + fin.y + fin.z + fin.w == 0.0f))) {
             // a non-finite g reaches the lines whose far zone holds its pixel and no others
 #pragma unroll
