@@ -117,20 +117,19 @@ bool split_rule(int N, int L, int D, int64_t evals) {
 // near zone, which the direct gather passes anyway.  Fewer than about 8,000
 // lines do not fill the chip, and the walk's length is what counts.  Split
 // against direct, 72 depths (us; in brackets the lines over a pixel):
-//   113 px: 3,000 lines 75 / 61 (35), 109 / 62 (9); 10,000 lines 126 / 135 (30);
-//           100,000 lines 891 / 951 (17); 30,000 lines 402 / 308 (5);
-//   360 px: 1,000 lines 107 / 122 (35), 180 / 121 (9), 582 / 147 (0.5);
-//           30,000 lines 446 / 690 (15); 10,000 lines 335 / 452 (5);
-//   3,600 px: 3,000 lines 783 / 1412 (16), 100 lines 893 / 1022 (9), 300 lines 2371 / 1290 (1.5);
-//   60 px: 30,000 lines 237 / 233 (45), 10,000 lines 116 / 93 (15).
+//   113 px: 3,000 lines 71 / 63 (35), 98 / 63 (9); 10,000 lines 121 / 135 (30); 30,000 251 / 348 (90);
+//   187 px: 10,000 lines 295 / 442 (5), 30,000 399 / 684 (15), 3,000 365 / 153 (1.6);
+//   350 px: 1,000 lines 95 / 124 (35), 153 / 121 (9), 100 lines 428 / 131 (0.9);
+//   1,800-3,300 px: 3,000 lines 647 / 1371 (16), 100 lines 735 / 1091 (9), 300 lines 1945 / 1126 (1.5);
+//   57 px: 30,000 lines 228 / 233 (45), 10,000 lines 111 / 93 (15).
 // With the centre test most lines of a dense catalogue are cut inside their
 // window at some depth, have no far zone and are summed directly either way,
 // so dense plans keep the direct gather (120,000 lines, 1560-1700 nm: 1.03 ms).
 bool split_gather_rule(int N, int L, int D, int64_t evals, bool center) {
     if (L == 0 || (center && L > N)) return false;
     const double window_px = (double)evals / D / L, over_px = window_px * L / N;
-    if (L >= 8000) return window_px >= 100.0 && over_px >= (window_px >= 200.0 ? 5.0 : 16.0);
-    return window_px >= 160.0 && over_px >= (window_px >= 1000.0 ? 10.0 : 25.0);
+    if (L >= 8000) return window_px >= 100.0 && over_px >= (window_px >= 150.0 ? 5.0 : 16.0);
+    return window_px >= 160.0 && over_px >= (window_px >= 1000.0 ? 6.0 : 25.0);
 }
 
 }  // namespace
