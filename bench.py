@@ -57,9 +57,9 @@ def log(*a):
 
 # The gather kernels' code: their bodies, the Voigt evaluator and the near
 # kernel's definition in pz_kernels.hip.
-GATHER_SOURCES = ("paper_2607_24141_amd/csrc/pz_split_gather.h", "paper_2607_24141_amd/csrc/pz_voigt.h",
-                  "paper_2607_24141_amd/csrc/voigt_consts.h")
-GATHER_DEF = ("paper_2607_24141_amd/csrc/pz_kernels.hip", "void k_gather_near(")
+GATHER_SOURCES = ("paper_2607_24141_amd/csrc/pz_split_gather.h", "paper_2607_24141_amd/csrc/pz_stages.h",
+                  "paper_2607_24141_amd/csrc/pz_voigt.h", "paper_2607_24141_amd/csrc/voigt_consts.h")
+GATHER_DEF = ("paper_2607_24141_amd/csrc/pz_kernels.hip", "void k_gather(")
 
 
 def kernel_hash(sources=KERNEL_SOURCES, definition=KERNEL_DEF):
@@ -338,7 +338,7 @@ def main():
         vg = _profile_json("valu_gather.json", gather_hash)
         if vg and "gather" in st_fb:
             tg = vg["flops_per_eval"] * plan.voigt_evals / (st_fb["gather"] * 1e-3) / 1e12
-            out["roofline_gather"] = {"bound": "alu", "kernel": "k_gather_far + k_gather_near", "achieved": tg, "peak": PEAK_FP32_TFLOPS,
+            out["roofline_gather"] = {"bound": "alu", "kernel": "k_gather_far + k_gather<true>", "achieved": tg, "peak": PEAK_FP32_TFLOPS,
                                       "unit": "TFLOP/s", "frac": tg / PEAK_FP32_TFLOPS,
                                       "flops_per_eval": vg["flops_per_eval"], "kernel_avg_ms": st_fb["gather"],
                                       "flops_source": "SQ VALU counters (profiles/valu_gather.json)"}
