@@ -29,7 +29,7 @@ Regions of z = v + i a (float32 unless noted):
   F^(n+1) = -2 v F^(n) - 2 n F^(n-1)):
       H = exp(a^2-u) cos(2av) + a [g + a^2 (s/3 + g (1 - 2u/3))
           + a^4 (s (7/30 - u/15) + g (1/2 - 2u/3 + 2u^2/15))],  s = 2/sqrt(pi),
-  so one table serves H and its derivatives.  g is piecewise cubic in |v|
+  so one table serves H.  g is piecewise cubic in |v|
   (intervals of 1/NEAR_INV, Chebyshev nodes, 4 floats each).
 * far zone of the split sums, v >= FAR_V and a <= FAR_AV v: with w = 1/v^2, b = a^2
       H = (a/sqrt(pi)) w sum_{n<=5} w^n P_n(b),
